@@ -57,27 +57,16 @@ REL = 1e-5
 # digest of the kernel sources it was measured on: after any change to them
 # the entry no longer matches and `traffic` is reported as null.
 MEASURED_TRAFFIC = {
-    # the default run: the 2,000,000-document 512^2 pass, kernel 3 (automatic)
+    # the default run: the 2,000,000-document 512^2 pass, list form (automatic)
     json.dumps(["map512x512-F20000-2M", [0, 1], 0, 262208, "f32", False, False, False, False,
                 {"group_tiles": 0, "kernel": 0, "lane_neurons": 0, "mask_mode": 0, "neuron_chunk": 0,
                  "schedule": 0, "slice_neurons": 0, "storage": 0, "sweep": 0, "tile_docs": 0}]): {
-        "csrc": "472a5147c0f0a07f",
-        "fetch_kib": [5.3876e9, 4.8234e9],       # per search launch (batch 0, batch 1)
-        "write_kib": [3.3554e7, 3.0446e7],
+        "csrc": "8cd428dd82aa5a22",
+        "fetch_kib": [3.0582e9, 2.7717e9],       # per search launch (batch 0, batch 1)
+        "write_kib": [8.1943e4, 7.4331e4],
         "fetch_scale": 2.0, "write_scale": 1.0,   # plain 4 GiB device copy: FETCH_SIZE reads half, WRITE_SIZE exact
-        "source": "rocprofv3 --pmc FETCH_SIZE, then WRITE_SIZE, k_search_st<float,8,4,8,16,2,2>, "
-                  "profiles/search_st_map512_2M_counters.md",
-    },
-    # batch 0 of the topic pass (--config 5 --batch 0), kernel 3 (automatic)
-    json.dumps(["map512x512-F20000-26.9M-topics", [0], 0, 262208, "f32", False, False, False, False,
-                {"group_tiles": 0, "kernel": 0, "lane_neurons": 0, "mask_mode": 0, "neuron_chunk": 0,
-                 "schedule": 0, "slice_neurons": 0, "storage": 0, "sweep": 0, "tile_docs": 0}]): {
-        "csrc": "472a5147c0f0a07f",
-        "fetch_kib": [1.3540e10],
-        "write_kib": [3.2000e7],
-        "fetch_scale": 2.0, "write_scale": 1.0,
-        "source": "rocprofv3 --pmc FETCH_SIZE, then WRITE_SIZE, k_search_st<float,8,4,8,16,2,2>, "
-                  "profiles/search_st_topics_1M_counters.md",
+        "source": "rocprofv3 --pmc FETCH_SIZE, then WRITE_SIZE, k_search_list<float,32>, "
+                  "profiles/search_list_map512_2M_counters.md",
     },
 }
 
@@ -310,6 +299,13 @@ def main():
         if not match:
             raise SystemExit("could not resolve the launch's kernel and tile size")
         kernel, unit_docs = match[0]
+        # the list form of the shared-union search stands in for the automatic
+        # kernel (in the same plan bytes) on batches of 1,536 documents and more
+        # (fp16: 1,024) when no knob names a kernel or a geometry
+        geometry = {k: v for k, v in knobs.items() if k not in ("storage", "sweep")}
+        f16 = args.weights == "f16"
+        if not any(geometry.values()) and F <= 65536 and Bmax >= (1024 if f16 else 1536):
+            kernel, unit_docs = 4, 128 if f16 else 256
 
     norms = torch.empty(N, dtype=torch.float32, device=dev)
     stream = torch.cuda.current_stream()
@@ -664,8 +660,8 @@ def main():
               "compulsory_hbm_vs_hbm_peak": comp_rate / HBM_PEAK_BPS}
     if probes:
         levels["l2_algorithmic_vs_measured_l2"] = l2_rate / (probes["l2_GBps"] * 1e9)
-    if kernel == 3 and not args.unfused:
-        # kernel 3 writes every union row slice into LDS once per super-tile
+    if kernel in (3, 4) and not args.unfused:
+        # these write every union row slice into LDS once per super-tile
         # (direct-to-LDS loads) and reads it from LDS once per membership
         lds_bytes = (float(sum(nnzs)) + float(union_total)) * N * wbytes
         levels["lds_algorithmic_vs_derived_lds_peak"] = lds_bytes / float(np.sum(search_s)) / LDS_PEAK_BPS
@@ -715,7 +711,7 @@ def main():
         },
         "roofline": {
             "kernel": ("k_search (union sweep writing the distance block) + k_argmin_rows" if args.unfused else
-                       {1: "k_search", 2: "k_search_docs", 3: "k_search_st"}[kernel]
+                       {1: "k_search", 2: "k_search_docs", 3: "k_search_st", 4: "k_search_list"}[kernel]
                        + " (fused union sweep + argmin) with key init and decode"),
             "bound": "l2",
             "achieved": l2_rate / 1e9,

@@ -84,6 +84,7 @@ struct Plan {
   int schedule = 1;          // 1 = one launch, 2 = round-synchronised launches (kernel 3)
   int chunk_slices = 1;      // kernels 1 and 3: neuron slices per schedule chunk
   bool rotate = false;       // kernel 3: rotated union sweeps (opts->sweep)
+  int list_docs = 0;         // > 0: the list form, documents per wave (see choose_lists)
 };
 
 // Kernel-1 tiles per workgroup chosen automatically: four consecutive tiles
@@ -222,8 +223,26 @@ size_t take(size_t& o, size_t bytes) {
 // positions [nnz]; kernel 3: features [nnz + pad], masks [nnz + pad][D / 32],
 // pad = 256 entries, plus 16 per tile with stage masks.
 struct PlanLayout {
-  size_t offset, count, feat, extra, total;
+  size_t offset, count, feat, extra, start, total;
 };
+
+// List plan (see launch_list_plan), inside the bytes of the automatic kernel's
+// own plan.
+int64_t list_tiles(int64_t B, int docs) { return (B + som::kListWaves * docs - 1) / (som::kListWaves * docs); }
+
+PlanLayout list_layout(int64_t B, int64_t nnz, int docs) {
+  PlanLayout l{};
+  const int64_t nt = list_tiles(B, docs);
+  const int64_t caps = nnz / som::kListRows + nt;   // each tile's nonzeros, rounded up
+  size_t o = 0;
+  l.offset = take(o, sizeof(int32_t) * (nt + 1));
+  l.count = take(o, sizeof(int32_t) * nt);
+  // the search reads whole 32-byte groups at the start of a list whatever its length
+  l.feat = take(o, static_cast<size_t>(caps) * som::kListCapBytes + 256);
+  l.start = take(o, sizeof(uint32_t) * (caps * som::kListWaves + nt + 4));
+  l.total = o;
+  return l;
+}
 
 PlanLayout plan_layout(const Plan& p, int64_t nnz) {
   PlanLayout l{};
@@ -238,6 +257,32 @@ PlanLayout plan_layout(const Plan& p, int64_t nnz) {
   l.extra = take(o, sizeof(int32_t) * (p.kernel == 3 ? (nnz + pad) * (p.D / 32) : nnz));
   l.total = o;
   return l;
+}
+
+// The automatic launch takes the list form of the shared-union search (tiles of
+// 256 documents for fp32, 128 for fp16) wherever its plan fits the bytes of the
+// kernel it stands in for (so buffer sizes do not depend on the choice), from
+// kListMinDocs documents on: below, too few workgroups fill the device (a
+// 2,048-document fp32 batch took 0.53 ms on the 128^2 map and 1.79 ms on 256^2
+// against kernel 3's 0.74 and 2.19; 1,024 documents 0.52 and 1.79 against 0.48
+// and 1.25; fp16, against kernel 1, 1,024 documents 0.20 and 0.60 against 0.23
+// and 0.68, 512 documents 0.19 and 0.58 against 0.16 and 0.43).  The choice
+// depends on the batch and F only, not on N, so that a plan serves any codebook
+// and column ranges of one compose exactly.  Any kernel or geometry knob keeps
+// the named kernel.
+constexpr int64_t kListMinDocsF32 = 1536, kListMinDocsF16 = 1024;
+
+void choose_lists(int64_t F, int64_t B, int64_t nnz, const som_bmu_opts* opts, int auto_weights, Plan* p) {
+  som_bmu_opts o{};
+  if (opts) o = *opts;
+  if (o.kernel || o.tile_docs || o.lane_neurons || o.group_tiles || o.mask_mode || o.slice_neurons ||
+      o.schedule == 2 || o.neuron_chunk)
+    return;
+  const bool f16 = auto_weights == som::kWeightsF16;
+  if (F > som::kListMaxF || B < (f16 ? kListMinDocsF16 : kListMinDocsF32)) return;
+  const int docs = f16 ? 16 : 32;
+  if (list_layout(B, nnz, docs).total > plan_layout(*p, nnz).total) return;
+  p->list_docs = docs;
 }
 
 // Packed keys: best [B] then second best [B] (the second array is used by
@@ -284,9 +329,18 @@ som_status run_validate(const int32_t* indptr, const int32_t* indices, int64_t B
   return SOM_OK;
 }
 
+// Where the plan's arrays lie for the chosen form.
+PlanLayout used_layout(const Plan& p, int64_t B, int64_t nnz) {
+  return p.list_docs ? list_layout(B, nnz, p.list_docs) : plan_layout(p, nnz);
+}
+
 hipError_t build_plan(const int32_t* indptr, const int32_t* indices, int64_t B, int64_t F,
                       const int32_t* perm, const Plan& p, void* plan, const PlanLayout& l,
                       hipStream_t stream) {
+  if (p.list_docs)
+    return som::launch_list_plan(indptr, indices, B, F, perm, p.list_docs, at<int32_t>(plan, l.offset),
+                                 at<int32_t>(plan, l.count), at<unsigned char>(plan, l.feat),
+                                 at<uint32_t>(plan, l.start), stream);
   if (p.kernel == 1 || p.kernel == 3)
     return som::launch_tile_plan(indptr, indices, B, F, perm, static_cast<int>(p.D), at<int32_t>(plan, l.offset),
                                  at<int32_t>(plan, l.count), at<int32_t>(plan, l.feat),
@@ -323,7 +377,15 @@ som_status run_planned(const void* W, int weights, int64_t F, int64_t N, int64_t
   a.tile_base = 0;
   a.tile_end = p.nunits;
   a.schedule = p.schedule;
-  if (p.kernel == 1 || p.kernel == 3) {
+  if (p.list_docs) {
+    a.kernel = 4;
+    a.T = p.list_docs;
+    a.ntiles = list_tiles(B, p.list_docs);
+    a.tile_offset = at<int32_t>(plan, l.offset);
+    a.tile_count = at<int32_t>(plan, l.count);
+    a.list_data = at<unsigned char>(plan, l.feat);
+    a.list_start = at<uint32_t>(plan, l.start);
+  } else if (p.kernel == 1 || p.kernel == 3) {
     a.tile_offset = at<int32_t>(plan, l.offset);
     a.tile_count = at<int32_t>(plan, l.count);
     a.union_feat = at<int32_t>(plan, l.feat);
@@ -431,9 +493,11 @@ static som_status search_impl(const void* W, int weights, int64_t F, int64_t N, 
     s = run_validate(indptr, indices, B, F, nnz, perm, at<int32_t>(ws, w.seen), at<int32_t>(ws, w.flag), stream);
     if (s != SOM_OK) return s;
   }
-  hipError_t e = build_plan(indptr, indices, B, F, perm, p, ws, w.plan, stream);
+  choose_lists(F, B, nnz, opts, weights, &p);
+  const PlanLayout l = used_layout(p, B, nnz);
+  hipError_t e = build_plan(indptr, indices, B, F, perm, p, ws, l, stream);
   if (e != hipSuccess) return hip_fail(e, "plan launch");
-  return run_planned(W, weights, F, N, ldw, norms, indptr, B, perm, ws, w.plan, bmu, dist, top2 ? bmu2 : nullptr,
+  return run_planned(W, weights, F, N, ldw, norms, indptr, B, perm, ws, l, bmu, dist, top2 ? bmu2 : nullptr,
                      dist2, p, at<uint64_t>(ws, w.keys), stream);
 }
 
@@ -571,7 +635,8 @@ som_status som_plan(const int32_t* indptr, const int32_t* indices, int64_t B, in
   if (!aligned(plan, 256)) return fail(SOM_ERR_INVALID_ARG, "plan must be 256-byte aligned");
   if (plan_bytes < l.total)
     return fail(SOM_ERR_WORKSPACE, "plan buffer too small: need " + std::to_string(l.total) + " bytes");
-  hipError_t e = build_plan(indptr, indices, B, F, perm, p, plan, l, stream);
+  choose_lists(F, B, nnz, opts, st, &p);
+  hipError_t e = build_plan(indptr, indices, B, F, perm, p, plan, used_layout(p, B, nnz), stream);
   if (e != hipSuccess) return hip_fail(e, "plan launch");
   return ok();
 }
@@ -608,7 +673,8 @@ static som_status planned_impl(const void* W, int weights, int64_t F, int64_t N,
   if (!aligned(ws, 256)) return fail(SOM_ERR_INVALID_ARG, "ws must be 256-byte aligned");
   if (ws_bytes < keys_bytes(B))
     return fail(SOM_ERR_WORKSPACE, "workspace too small: need " + std::to_string(keys_bytes(B)) + " bytes");
-  return run_planned(W, weights, F, N, ldw, norms, indptr, B, perm, plan, l, bmu, dist, top2 ? bmu2 : nullptr, dist2,
+  choose_lists(F, B, nnz, opts, opts_storage(opts), &p);
+  return run_planned(W, weights, F, N, ldw, norms, indptr, B, perm, plan, used_layout(p, B, nnz), bmu, dist, top2 ? bmu2 : nullptr, dist2,
                      p, static_cast<uint64_t*>(ws), stream);
 }
 

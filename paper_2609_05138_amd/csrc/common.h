@@ -58,6 +58,30 @@ hipError_t launch_tile_plan(const int32_t* indptr, const int32_t* indices, int64
                             int32_t* union_feat, uint32_t* union_mask, hipStream_t stream,
                             bool stage_masks = false);
 
+// List plan (for the list form of the shared-union search, search_list.h), in
+// tiles of kListWaves * DW documents: a tile's feature union in ascending order,
+// cut into stages of kListRows, and per (stage, wave) a list of 16-bit entries,
+// one per membership: the document's place in the wave in the low bits, the
+// row's slot offset (a multiple of kListRowBytes) above; padded to whole units
+// of four.  Space is counted in stage capacities: ceil(nnz / kListRows) per tile
+// bound its stages (a union row has a nonzero); tile_offset is their exclusive
+// scan, tile_count the stages in use.  A tile's bytes in `data` start at
+// tile_offset * kListCapBytes: the ids of its stages (int32, padded with 0),
+// then its lists.  Its words of `start` begin at tile_offset * kListWaves + t:
+// the start of list i = stage * kListWaves + wave, in units from the tile's
+// first list; list i + 1 follows.
+constexpr int kListWaves = 8;
+constexpr int kListRows = 64;
+constexpr int kListRowBytes = 512;
+constexpr int kListCapBytes = kListRows * (4 + 2) + kListWaves * 3 * 2;
+constexpr int kListStageWork = 128;  // a stage's fixed cost in entries, for the phase of rotated sweeps
+constexpr int kListPhaseWgs = 96;    // phase period in workgroups per XCD
+constexpr int64_t kListMaxF = 65536;  // the plan kernel's tables fit the LDS
+static_assert(kListCapBytes % 16 == 0, "a tile's ids are read 16 bytes at a time");
+hipError_t launch_list_plan(const int32_t* indptr, const int32_t* indices, int64_t B, int64_t F,
+                            const int32_t* perm, int DW, int32_t* tile_offset, int32_t* tile_count,
+                            unsigned char* data, uint32_t* start, hipStream_t stream);
+
 // Document-group plan (for the documents-on-lanes search): per group of D
 // consecutive documents of the tiled order, the sorted feature union and the
 // union position of every nonzero.
@@ -128,11 +152,14 @@ struct SearchArgs {
   const int32_t* tile_count;
   const int32_t* union_feat;
   const uint32_t* union_mask;
+  const unsigned char* list_data;   // list form (kernel 4)
+  const uint32_t* list_start;
   uint64_t* keys;   // [B] packed (distance, index) minima, tiled order
   uint64_t* keys2;  // [B] second-smallest keys, or nullptr when only the BMU is wanted
   // documents-on-lanes search (kernel 2)
   int kernel;       // 1 = neurons on lanes (tile masks), 2 = documents on lanes (groups),
-                    // 3 = shared-union super-tiles (tile plan with group * T / 32 mask words)
+                    // 3 = shared-union super-tiles (tile plan with group * T / 32 mask words),
+                    // 4 = their list form (list plan, T documents per wave)
   int slice;        // kernel 2: neurons per slice (32 or 64)
   const int32_t* group_offset;
   const int32_t* group_count;
@@ -148,6 +175,7 @@ hipError_t launch_search(const SearchArgs& a, hipStream_t stream);
 // Kernels 1 and 3 over an fp16 codebook (their own translation unit).
 hipError_t launch_search_k1_f16(const SearchArgs& a, hipStream_t stream);
 hipError_t launch_search_st_f16(const SearchArgs& a, hipStream_t stream);
+hipError_t launch_search_list_f16(const SearchArgs& a, hipStream_t stream);
 // Unfused comparator: kernel 1 writes the distance block of block_docs
 // documents at a time into `score`, then a wave-per-row argmin reduces it.
 hipError_t launch_unfused(SearchArgs a, int64_t block_docs, hipStream_t stream);

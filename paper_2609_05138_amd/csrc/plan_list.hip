@@ -1,0 +1,262 @@
+// List plan (paper, Section 4.1, with a tile of kListWaves * DW documents; the
+// arrays are laid out in common.h): per tile the sorted feature union, and per
+// (stage of kListRows union rows, wave) the list of its documents' memberships
+// that search_list.h walks.
+//
+// One workgroup of kListWaves waves per tile.  The union is a bitmap over the
+// features in LDS; with a prefix count per word, a feature's union row is one
+// LDS read and a bit count.  Wave w reads its DW documents' features three
+// times (they stay in the L2): to mark the bitmap, to count its memberships per
+// stage, and to place them; a document's features ascend, so those of one stage
+// are a run of neighbouring lanes whose first lane owns the counter.  Only wave
+// w touches list (stage, w), in document order, so the plan is the same on
+// every run.  Bound: the latency of the document reads (perm, indptr, then
+// indices), which four documents in flight per wave and several workgroups per
+// CU hide.
+#include "common.h"
+
+namespace som {
+namespace {
+
+constexpr int kThreads = kListWaves * 64;
+constexpr int S = kListWaves, R = kListRows;
+
+// Stage capacities of each tile.  One wave per tile.
+__global__ void __launch_bounds__(256)
+k_list_nnz(const int32_t* __restrict__ indptr, const int32_t* __restrict__ perm, int64_t B, int D, int64_t ntiles,
+           int32_t* __restrict__ tile_caps) {
+  const int64_t t = static_cast<int64_t>(blockIdx.x) * 4 + (threadIdx.x >> 6);
+  if (t >= ntiles) return;
+  const int lane = threadIdx.x & 63;
+  int32_t s = 0;
+  for (int k = lane; k < D; k += 64) {
+    const int64_t p = t * D + k;
+    if (p < B) {
+      const int64_t d = perm ? static_cast<int64_t>(perm[p]) : p;
+      s += indptr[d + 1] - indptr[d];
+    }
+  }
+#pragma unroll
+  for (int off = 32; off >= 1; off >>= 1) s += __shfl_xor(s, off, 64);
+  if (lane == 0) tile_caps[t] = static_cast<int32_t>((static_cast<int64_t>(s) + R - 1) / R);
+}
+
+// Exclusive scan of n values into out[0..n] (out[n] = total), one workgroup of
+// 1024 threads: 1024 values per step, so the loads stay coalesced.
+__global__ void __launch_bounds__(1024)
+k_list_scan(const int32_t* __restrict__ in, int64_t n, int32_t* __restrict__ out) {
+  __shared__ int32_t wsum[16];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  int32_t carry = 0;
+  for (int64_t i0 = 0; i0 < n; i0 += 1024) {
+    const int64_t i = i0 + tid;
+    const int32_t v = i < n ? in[i] : 0;
+    int32_t x = v;
+#pragma unroll
+    for (int off = 1; off < 64; off <<= 1) {
+      const int32_t y = __shfl_up(x, off, 64);
+      x += lane >= off ? y : 0;
+    }
+    if (lane == 63) wsum[wave] = x;
+    __syncthreads();
+    int32_t before = carry, total = 0;
+#pragma unroll
+    for (int w = 0; w < 16; ++w) {
+      const int32_t y = wsum[w];
+      before += w < wave ? y : 0;
+      total += y;
+    }
+    if (i < n) out[i] = before + x - v;
+    carry += total;
+    __syncthreads();
+  }
+  if (tid == 0) out[n] = carry;
+}
+
+// Exclusive scan of one value per thread over the workgroup.
+__device__ __forceinline__ int32_t block_scan(int32_t v, int32_t* wsum, int32_t* total) {
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  int32_t x = v;
+#pragma unroll
+  for (int off = 1; off < 64; off <<= 1) {
+    const int32_t y = __shfl_up(x, off, 64);
+    x += lane >= off ? y : 0;
+  }
+  if (lane == 63) wsum[wave] = x;
+  __syncthreads();
+  int32_t before = 0, sum = 0;
+#pragma unroll
+  for (int w = 0; w < kListWaves; ++w) {
+    const int32_t y = wsum[w];
+    before += w < wave ? y : 0;
+    sum += y;
+  }
+  __syncthreads();
+  *total = sum;
+  return before + x - v;
+}
+
+// Calls fn(feature, active lane, document of the wave) over the wave's
+// documents in order, a document's features in ascending order, 64 at a time;
+// every lane of the wave takes part in each call.
+template <int DW, typename Fn>
+__device__ __forceinline__ void for_each_feature(const int32_t* __restrict__ indices, int32_t begin, int32_t end,
+                                                 int lane, Fn fn) {
+#pragma unroll 1
+  for (int s0 = 0; s0 < DW; s0 += 4) {
+    int32_t b[4], e[4], f[4];
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      b[k] = __builtin_amdgcn_readlane(begin, s0 + k);
+      e[k] = __builtin_amdgcn_readlane(end, s0 + k);
+      f[k] = b[k] + lane < e[k] ? indices[b[k] + lane] : 0;
+    }
+    int32_t g[4];
+#pragma unroll
+    for (int k = 0; k < 4; ++k) g[k] = b[k] + 64 + lane < e[k] ? indices[b[k] + 64 + lane] : 0;
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      if (b[k] < e[k]) fn(f[k], b[k] + lane < e[k], s0 + k);
+      if (b[k] + 64 < e[k]) fn(g[k], b[k] + 64 + lane < e[k], s0 + k);
+      for (int32_t i = b[k] + 128; i < e[k]; i += 64) fn(i + lane < e[k] ? indices[i + lane] : 0, i + lane < e[k], s0 + k);
+    }
+  }
+}
+
+template <int DW>
+__global__ void __launch_bounds__(kThreads)
+k_list_plan(const int32_t* __restrict__ indptr, const int32_t* __restrict__ indices, const int32_t* __restrict__ perm,
+            int64_t B, int32_t words, const int32_t* __restrict__ tile_offset, int32_t* __restrict__ tile_count,
+            unsigned char* __restrict__ data, uint32_t* __restrict__ start) {
+  extern __shared__ uint32_t lds[];
+  uint32_t* bits = lds;                       // [words] the union
+  uint32_t* before = lds + words;             // [words] union rows in earlier words
+  volatile int32_t* list = reinterpret_cast<volatile int32_t*>(lds + 2 * words);  // [stages * S] lengths, then cursors
+  __shared__ int32_t wsum[kListWaves];
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int64_t t = blockIdx.x;
+  const int64_t cap0 = tile_offset[t];
+  unsigned char* base = data + cap0 * kListCapBytes;
+  int32_t* ids = reinterpret_cast<int32_t*>(base);
+  int32_t begin = 0, end = 0;
+  {
+    const int64_t p = t * (S * DW) + wave * DW + lane;
+    if (lane < DW && p < B) {
+      const int64_t d = perm ? static_cast<int64_t>(perm[p]) : p;
+      begin = indptr[d];
+      end = indptr[d + 1];
+    }
+  }
+  for (int i = tid; i < words; i += kThreads) bits[i] = 0u;
+  __syncthreads();
+  for_each_feature<DW>(indices, begin, end, lane, [&](int32_t f, bool on, int) {
+    if (on) atomicOr(&bits[f >> 5], 1u << (f & 31));
+  });
+  __syncthreads();
+  // prefix counts over a contiguous run of words per thread, and the ids
+  const int per = (words + kThreads - 1) / kThreads;
+  const int w0 = tid * per, w1 = w0 + per < words ? w0 + per : words;
+  int32_t c = 0;
+  for (int i = w0; i < w1; ++i) c += __popc(bits[i]);
+  int32_t cnt;
+  int32_t u = block_scan(c, wsum, &cnt);
+  const int32_t nst = (cnt + R - 1) / R;
+  for (int i = w0; i < w1; ++i) {
+    before[i] = static_cast<uint32_t>(u);
+    for (uint32_t m = bits[i]; m; m &= m - 1) ids[u++] = i * 32 + __builtin_ctz(m);
+  }
+  for (int i = cnt + tid; i < nst * R; i += kThreads) ids[i] = 0;
+  for (int i = tid; i < nst * S; i += kThreads) list[i] = 0;
+  if (tid == 0) tile_count[t] = nst;
+  __syncthreads();
+
+  // runs of one stage within a call: the first lane of each (leader), its
+  // length, and each lane's place in its run
+  struct Run {
+    int32_t row, list, length, place;
+    bool leader;
+  };
+  auto run_of = [&](int32_t f, bool on) {
+    Run r;
+    const uint32_t w = bits[f >> 5];
+    r.row = static_cast<int32_t>(before[f >> 5]) + __popc(w & ((1u << (f & 31)) - 1u));
+    const int32_t stage = on ? r.row / R : -1;
+    r.list = stage * S + wave;
+    const int32_t prev = __shfl_up(stage, 1, 64);
+    r.leader = on && (lane == 0 || prev != stage);
+    const uint64_t leaders = __ballot(r.leader);
+    const int active = __popcll(__ballot(on));         // the lanes with a feature come first
+    const uint64_t upto = (((1ull << lane) - 1ull) << 1) | 1ull;
+    const uint64_t later = leaders & ~upto;
+    r.length = (later ? __builtin_ctzll(later) : active) - lane;
+    r.place = lane - (63 - __builtin_clzll((leaders & upto) | 1ull));
+    return r;
+  };
+  for_each_feature<DW>(indices, begin, end, lane, [&](int32_t f, bool on, int) {
+    const Run r = run_of(f, on);
+    if (r.leader) list[r.list] += r.length;
+  });
+  __syncthreads();
+  // starts of the lists in units of four entries; lengths become cursors
+  uint32_t* st = start + cap0 * S + t;
+  int32_t units = 0;
+  for (int i0 = 0; i0 < nst * S; i0 += kThreads) {
+    const int i = i0 + tid;
+    const int32_t v = i < nst * S ? (list[i] + 3) / 4 : 0;
+    int32_t sum;
+    const int32_t at = units + block_scan(v, wsum, &sum);
+    if (i < nst * S) {
+      st[i] = static_cast<uint32_t>(at);
+      list[i] = at * 4;
+    }
+    units += sum;
+  }
+  if (tid == 0) st[nst * S] = static_cast<uint32_t>(units);
+  __syncthreads();
+  uint16_t* entries = reinterpret_cast<uint16_t*>(base + nst * (R * 4));
+  for_each_feature<DW>(indices, begin, end, lane, [&](int32_t f, bool on, int s) {
+    const Run r = run_of(f, on);
+    if (on) {
+      // slot row of union row k of the stage: the search loads rows 4 * half +
+      // i of each wave's eight as its i-th pair
+      const int32_t k = r.row % R;
+      const int32_t slot_row = (k & ~7) | ((k & 3) << 1) | ((k >> 2) & 1);
+      entries[list[r.list] + r.place] = static_cast<uint16_t>(slot_row * kListRowBytes + s);
+    }
+    __builtin_amdgcn_wave_barrier();
+    if (r.leader) list[r.list] += r.length;   // after every lane's read: LDS operations of a wave keep their order
+    __builtin_amdgcn_wave_barrier();
+  });
+  __syncthreads();
+  for (int i = tid; i < nst * S; i += kThreads)
+    for (int32_t k = list[i]; k & 3; ++k) entries[k] = static_cast<uint16_t>(DW);   // slot row 0 into the spare register
+}
+
+}  // namespace
+
+hipError_t launch_list_plan(const int32_t* indptr, const int32_t* indices, int64_t B, int64_t F,
+                            const int32_t* perm, int DW, int32_t* tile_offset, int32_t* tile_count,
+                            unsigned char* data, uint32_t* start, hipStream_t stream) {
+  if (F > kListMaxF || (DW != 16 && DW != 32)) return hipErrorInvalidValue;
+  const int D = S * DW;
+  const int64_t ntiles = (B + D - 1) / D;
+  hipLaunchKernelGGL(k_list_nnz, dim3(static_cast<uint32_t>((ntiles + 3) / 4)), dim3(256), 0, stream, indptr, perm, B,
+                     D, ntiles, tile_count);
+  hipLaunchKernelGGL(k_list_scan, dim3(1), dim3(1024), 0, stream, tile_count, ntiles, tile_offset);
+  const int32_t words = static_cast<int32_t>((F + 31) / 32);
+  const int64_t stages = (F + R - 1) / R;
+  const size_t bytes = sizeof(uint32_t) * (2 * static_cast<size_t>(words) + static_cast<size_t>(stages) * S);
+  const void* fn = DW == 16 ? reinterpret_cast<const void*>(k_list_plan<16>) : reinterpret_cast<const void*>(k_list_plan<32>);
+  hipError_t e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(bytes));
+  if (e != hipSuccess) return e;
+  if (DW == 16)
+    hipLaunchKernelGGL(k_list_plan<16>, dim3(static_cast<uint32_t>(ntiles)), dim3(kThreads), bytes, stream, indptr,
+                       indices, perm, B, words, tile_offset, tile_count, data, start);
+  else
+    hipLaunchKernelGGL(k_list_plan<32>, dim3(static_cast<uint32_t>(ntiles)), dim3(kThreads), bytes, stream, indptr,
+                       indices, perm, B, words, tile_offset, tile_count, data, start);
+  return hipGetLastError();
+}
+
+}  // namespace som

@@ -1,7 +1,7 @@
 // Fused BMU search, kernel 2 (documents on lanes), the key array
 // initialisation and decode, and the dispatch of the three kernels (paper,
 // Section 3; kernel 1 is in search_k1.h, kernel 3 in search_st.h).
-#include "search_st.h"
+#include "search_list.h"
 
 namespace som {
 namespace {
@@ -349,11 +349,19 @@ hipError_t launch_k3(const SearchArgs& a, hipStream_t stream) {
   return hipErrorInvalidValue;
 }
 
+hipError_t launch_k4(const SearchArgs& a, hipStream_t stream) {
+  if (a.weights == kWeightsF16) return launch_search_list_f16(a, stream);
+  if (a.T == 32) return launch_list<float, 32>(a, stream);
+  if (a.T == 16) return launch_list<float, 16>(a, stream);   // on a plan made for fp16
+  return hipErrorInvalidValue;
+}
+
 hipError_t launch_search(const SearchArgs& a, hipStream_t stream) {
   hipLaunchKernelGGL(k_keys_init, dim3(static_cast<uint32_t>((a.B + 255) / 256)), dim3(256), 0, stream,
                      a.keys, a.keys2, a.B);
   if (a.kernel == 2) return launch_docs(a, stream);
   if (a.kernel == 3) return launch_k3(a, stream);
+  if (a.kernel == 4) return launch_k4(a, stream);
   return launch_k1(a, stream);
 }
 

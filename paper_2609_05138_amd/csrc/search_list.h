@@ -1,0 +1,456 @@
+// List form of the shared-union search: wide tiles, narrow slices, and
+// per-wave lists of (row, document) entries.
+//
+// A workgroup of S = 8 waves takes D = S * DW consecutive documents of the
+// tiled order and one slice of 64 * NPL neurons whose rows are 512 bytes
+// (128 fp32 or 256 fp16 neurons).  The tile's feature union is swept once, in
+// stages of R = 64 rows held in a two-slot LDS ring (64 KB, two workgroups per
+// CU), each wave moving its eight rows of a stage with four direct
+// global-to-LDS loads.  Wave w owns documents w*DW .. w*DW+DW-1; a lane keeps
+// NPL neurons of each in registers.  The plan stores, per stage and wave, the
+// stage's (row, document) memberships as 16-bit entries (row offset in the
+// slot | document), per document in ascending row order, padded to whole units
+// of four with entries that add row 0 into a spare register.  A wave walks its
+// list from scalar registers: per entry one vector instruction forms the LDS
+// address, one LDS read fetches the lane's NPL weights, and NPL adds, whose
+// accumulator is named through the VGPR index register, fold them in.  A
+// unit's reads are issued before the previous unit's adds.
+//
+// What bounds it: vector issue and the LDS reads, three vector instructions and
+// 512 bytes per entry (on the 512^2 map a 262,144-document batch spends about
+// 260 of its 525 ms in the lists, the rest in stage barriers and the stages'
+// fixed instructions; the row loads alone take 300 ms and overlap).  Kernel 3
+// took 545 ms there: its 64-document tiles of 256-neuron slices need 484 ms of
+// row loads (33.6 rows per document at a working set of 20 MB per slice against
+// 21.7 rows at 10 MB) and a scalar test per document and 16-row stage.  On the
+// 512^2 topic batch, which the row loads bound, 131,072 documents took 449 ms
+// (kernel 3: 648); the 128^2 map's 65,536-document search 8.4 ms (11.0).
+// Measured and not kept: rows held by one document loaded straight into
+// registers by the document's wave (575 ms: the loads wait for each other, where
+// the staged ones are in flight together), and scalar copies of the next list's
+// first entries instead of loading them inside the list's own statement.
+//
+// Sweep order: as kernel 3's rotated sweep (see search_st.h), with the phase
+// taken in work (list entries and rows), or ascending; either way a
+// document's dot product is summed in the sweep's order, one fp32 add per
+// feature, so the ascending sweep gives every kernel's bits.
+#pragma once
+
+#include <type_traits>
+
+#include "search_st.h"
+
+namespace som {
+namespace {
+
+typedef float f32x16v __attribute__((ext_vector_type(16)));
+typedef float f32x32v __attribute__((ext_vector_type(32)));
+typedef uint32_t u32x8v __attribute__((ext_vector_type(8)));
+typedef int32_t i32x4v __attribute__((ext_vector_type(4)));
+
+// ---------------------------------------------------------------------------
+// A wave's list of one stage, as one inline-assembly statement.
+//
+// Registers: s[32:39] (s[40:47] in odd steps) and s[48:55] hold 16 entries (four
+// units) each, reloaded alternately; s56-s59 hold the odd entries of the unit
+// being added and of the next one, shifted down.  Rows land in v[24:31] (even
+// units) and v[32:39] (odd units).  The statement also loads the next stage's
+// first set into the other parity's registers.  The accumulators start at v40,
+// one plane of DW registers per neuron of the lane, planes DW + 2 registers
+// apart; register DW of a plane takes the padding.  Scalar loads and LDS reads
+// share one counter and return out of order with each other, so every wait for
+// them is for zero; a unit's wait falls after the whole adds of the unit before.
+// Every load is waited for before the statement ends.
+// ---------------------------------------------------------------------------
+#define SOM_L_RD(S, R, R1) \
+  "v_and_or_b32 v" #R ", s" #S ", %[vm], %[vl]\n\tds_read_b64 v[" #R ":" #R1 "], v" #R "\n\t"
+#define SOM_L_ISSUE0(A, B)                                                               \
+  SOM_L_RD(A, 24, 25) "s_lshr_b32 s56, s" #A ", 16\n\t" SOM_L_RD(56, 26, 27)             \
+  SOM_L_RD(B, 28, 29) "s_lshr_b32 s57, s" #B ", 16\n\t" SOM_L_RD(57, 30, 31)
+#define SOM_L_ISSUE1(A, B)                                                               \
+  SOM_L_RD(A, 32, 33) "s_lshr_b32 s58, s" #A ", 16\n\t" SOM_L_RD(58, 34, 35)             \
+  SOM_L_RD(B, 36, 37) "s_lshr_b32 s59, s" #B ", 16\n\t" SOM_L_RD(59, 38, 39)
+#define SOM_L_IDX(S) "s_set_gpr_idx_idx s" #S "\n\t"
+// four adds: entries (or singles) S0..S3, rows from v R, R + 2, ..
+#define SOM_L_ADD4(S0, S1, S2, S3, R0, R1, R2, R3, R4, R5, R6, R7)                          \
+  "s_set_gpr_idx_on s" #S0 ", " SOM_L_MODE "\n\t" SOM_L_ADD(R0, R1) SOM_L_IDX(S1)           \
+      SOM_L_ADD(R2, R3) SOM_L_IDX(S2) SOM_L_ADD(R4, R5) SOM_L_IDX(S3) SOM_L_ADD(R6, R7) "s_set_gpr_idx_off\n\t"
+#define SOM_L_ADDS0(A, B) SOM_L_ADD4(A, 56, B, 57, 24, 25, 26, 27, 28, 29, 30, 31)
+#define SOM_L_ADDS1(A, B) SOM_L_ADD4(A, 58, B, 59, 32, 33, 34, 35, 36, 37, 38, 39)
+// unit in dwords A, B, next unit's dwords NA, NB; n counts the units after
+// this one (its borrow ends the list)
+#define SOM_L_UNIT0(LBL, LOAD, A, B, NA, NB)                                            \
+  "s_waitcnt lgkmcnt(0)\n\t" LOAD "s_sub_u32 %[n], %[n], 1\n\ts_cbranch_scc1 " LBL "\n\t" \
+      SOM_L_ISSUE1(NA, NB) SOM_L_ADDS0(A, B)
+#define SOM_L_UNIT1(LBL, LOAD, A, B, NA, NB)                                            \
+  "s_waitcnt lgkmcnt(0)\n\t" LOAD "s_sub_u32 %[n], %[n], 1\n\ts_cbranch_scc1 " LBL "\n\t" \
+      SOM_L_ISSUE0(NA, NB) SOM_L_ADDS1(A, B)
+#define SOM_L_LAST0(LBL, A, B) LBL ":\n\t" SOM_L_ADDS0(A, B) "s_branch .Lsom_end%=\n"
+#define SOM_L_LAST1(LBL, A, B) LBL ":\n\t" SOM_L_ADDS1(A, B) "s_branch .Lsom_end%=\n"
+#define SOM_L_LB(K) ".Lsom_u" #K "_%="
+// reload of an entry set when four or more units follow (n as above)
+#define SOM_L_RELOAD(K, SET, OFF)                                                          \
+  "s_cmp_lt_u32 %[n], 4\n\ts_cbranch_scc1 .Lsom_l" #K "_%=\n\ts_load_dwordx8 " SET ", %[lb], %[eo] offset:" OFF "\n.Lsom_l" #K "_%=:\n\t"
+// SET, A0..A7: the first entry set; NSET: the next stage's
+#define SOM_L_BODY(SET, NSET, A0, A1, A2, A3, A4, A5, A6, A7)                              \
+  "s_load_dwordx8 " NSET ", %[lb], %[neo]\n\t"                                             \
+  "s_cmp_eq_u32 %[n], -1\n\ts_cbranch_scc1 .Lsom_end%=\n\t"                                \
+  SOM_L_ISSUE0(A0, A1)                                                                     \
+  ".Lsom_top%=:\n\t"                                                                       \
+  SOM_L_UNIT0(SOM_L_LB(0), SOM_L_RELOAD(0, "s[48:55]", "0x20"), A0, A1, A2, A3)            \
+  SOM_L_UNIT1(SOM_L_LB(1), "", A2, A3, A4, A5)                                             \
+  SOM_L_UNIT0(SOM_L_LB(2), "", A4, A5, A6, A7)                                             \
+  SOM_L_UNIT1(SOM_L_LB(3), "", A6, A7, 48, 49)                                             \
+  SOM_L_UNIT0(SOM_L_LB(4), SOM_L_RELOAD(4, SET, "0x40"), 48, 49, 50, 51)                   \
+  SOM_L_UNIT1(SOM_L_LB(5), "", 50, 51, 52, 53)                                             \
+  SOM_L_UNIT0(SOM_L_LB(6), "", 52, 53, 54, 55)                                             \
+  SOM_L_UNIT1(SOM_L_LB(7), "", 54, 55, A0, A1)                                             \
+  "s_add_u32 %[eo], %[eo], 0x40\n\ts_branch .Lsom_top%=\n"                                 \
+  SOM_L_LAST0(SOM_L_LB(0), A0, A1) SOM_L_LAST1(SOM_L_LB(1), A2, A3)                        \
+  SOM_L_LAST0(SOM_L_LB(2), A4, A5) SOM_L_LAST1(SOM_L_LB(3), A6, A7)                        \
+  SOM_L_LAST0(SOM_L_LB(4), 48, 49) SOM_L_LAST1(SOM_L_LB(5), 50, 51)                        \
+  SOM_L_LAST0(SOM_L_LB(6), 52, 53) SOM_L_LAST1(SOM_L_LB(7), 54, 55)                        \
+  ".Lsom_end%=:\n\ts_waitcnt lgkmcnt(0)\n\t"
+#define SOM_L_EVEN SOM_L_BODY("s[32:39]", "s[40:47]", 32, 33, 34, 35, 36, 37, 38, 39)
+#define SOM_L_ODD SOM_L_BODY("s[40:47]", "s[32:39]", 40, 41, 42, 43, 44, 45, 46, 47)
+#define SOM_L_CLOBBERS                                                                                             \
+  "v24", "v25", "v26", "v27", "v28", "v29", "v30", "v31", "v32", "v33", "v34", "v35", "v36", "v37", "v38", "v39",  \
+      "s48", "s49", "s50", "s51", "s52", "s53", "s54", "s55", "s56", "s57", "s58", "s59", "scc", "memory"
+
+// Accumulators of a wave: plane q holds neuron q of the lane for each document.
+template <int DW, int NPL>
+struct ListAcc;
+template <int NPL>
+struct ListAcc<32, NPL> {
+  f32x32v p[NPL];
+};
+template <int NPL>
+struct ListAcc<16, NPL> {
+  f32x16v p[NPL];
+};
+
+// Adds a stage's list and loads the next one's first set.  lb: the tile's
+// lists; eo, neo: byte offsets of this stage's list and the next one's; n: units
+// of four entries, less one; vl: the slot's base | the lane's byte offset in a
+// row; vm: the mask of an entry's row offset.
+#define SOM_L_OPERANDS(SET, NSET) "={m0}"(m0), SET(set), NSET(nset), [eo] "+s"(eo), [n] "+s"(n), SOM_L_ACC
+#define SOM_L_INPUTS [lb] "s"(lb), [neo] "s"(neo), [vl] "v"(vl), [vm] "v"(vm)
+// (the index register is M0)
+#define SOM_L_DEFINE(DW, NPL)                                                                                       \
+  template <bool ODD>                                                                                               \
+  __device__ __forceinline__ u32x8v add_list(ListAcc<DW, NPL>& acc, u32x8v set, uint64_t lb, uint32_t eo,           \
+                                             uint32_t neo, uint32_t n, uint32_t vl, uint32_t vm) {                  \
+    u32x8v nset;                                                                                                    \
+    uint32_t m0;                                                                                                    \
+    if constexpr (ODD)                                                                                              \
+      asm volatile(SOM_L_ODD                                                                                        \
+                   : SOM_L_OPERANDS("+{s[40:47]}", "=&{s[32:39]}") : SOM_L_INPUTS : SOM_L_CLOBBERS, SOM_L_SPARE);   \
+    else                                                                                                            \
+      asm volatile(SOM_L_EVEN                                                                                       \
+                   : SOM_L_OPERANDS("+{s[32:39]}", "=&{s[40:47]}") : SOM_L_INPUTS : SOM_L_CLOBBERS, SOM_L_SPARE);   \
+    return nset;                                                                                                    \
+  }
+// fp32 rows: two neurons per lane
+#define SOM_L_MODE "gpr_idx(SRC0,DST)"
+#define SOM_L_ADD(R, R1) "v_add_f32_e32 v40, v40, v" #R "\n\tv_add_f32_e32 v74, v74, v" #R1 "\n\t"
+#define SOM_L_ACC "+{v[40:71]}"(acc.p[0]), "+{v[74:105]}"(acc.p[1])
+#define SOM_L_SPARE "v72", "v106"
+SOM_L_DEFINE(32, 2)
+#undef SOM_L_ADD
+#undef SOM_L_ACC
+#undef SOM_L_SPARE
+#define SOM_L_ADD(R, R1) "v_add_f32_e32 v40, v40, v" #R "\n\tv_add_f32_e32 v58, v58, v" #R1 "\n\t"
+#define SOM_L_ACC "+{v[40:55]}"(acc.p[0]), "+{v[58:73]}"(acc.p[1])
+#define SOM_L_SPARE "v56", "v74"
+SOM_L_DEFINE(16, 2)
+#undef SOM_L_ADD
+#undef SOM_L_ACC
+#undef SOM_L_SPARE
+#undef SOM_L_MODE
+// fp16 rows: four neurons per lane, each half widened and added by one fused
+// multiply-add with 1.0 (exact product, one rounding: the widened add)
+#define SOM_L_MODE "gpr_idx(SRC2,DST)"
+#define SOM_L_MIX(P, R, HI) \
+  "v_fma_mix_f32 v" #P ", v" #R ", 1.0, v" #P " op_sel:[" #HI ",0,0] op_sel_hi:[1,0,0]\n\t"
+#define SOM_L_ADD(R, R1) SOM_L_MIX(40, R, 0) SOM_L_MIX(58, R, 1) SOM_L_MIX(76, R1, 0) SOM_L_MIX(94, R1, 1)
+#define SOM_L_ACC "+{v[40:55]}"(acc.p[0]), "+{v[58:73]}"(acc.p[1]), "+{v[76:91]}"(acc.p[2]), "+{v[94:109]}"(acc.p[3])
+#define SOM_L_SPARE "v56", "v74", "v92", "v110"
+SOM_L_DEFINE(16, 4)
+#undef SOM_L_ADD
+#undef SOM_L_ACC
+#undef SOM_L_SPARE
+#define SOM_L_ADD(R, R1) SOM_L_MIX(40, R, 0) SOM_L_MIX(74, R, 1) SOM_L_MIX(108, R1, 0) SOM_L_MIX(142, R1, 1)
+#define SOM_L_ACC "+{v[40:71]}"(acc.p[0]), "+{v[74:105]}"(acc.p[1]), "+{v[108:139]}"(acc.p[2]), "+{v[142:173]}"(acc.p[3])
+#define SOM_L_SPARE "v72", "v106", "v140", "v174"
+SOM_L_DEFINE(32, 4)
+#undef SOM_L_ADD
+#undef SOM_L_ACC
+#undef SOM_L_SPARE
+#undef SOM_L_MODE
+
+// Minimum of x over the wave, uniform (data-parallel-primitive row shifts, then
+// the two row broadcasts: lane 63 ends with the whole wave's).
+__device__ __forceinline__ uint32_t wave_min_u32(uint32_t x) {
+#define SOM_DPP_MIN(CTRL, ROWS)                                                                   \
+  {                                                                                               \
+    const uint32_t y_ = static_cast<uint32_t>(                                                    \
+        __builtin_amdgcn_update_dpp(-1, static_cast<int>(x), CTRL, ROWS, 0xf, false));            \
+    x = y_ < x ? y_ : x;                                                                          \
+  }
+  SOM_DPP_MIN(0x111, 0xf)
+  SOM_DPP_MIN(0x112, 0xf)
+  SOM_DPP_MIN(0x114, 0xf)
+  SOM_DPP_MIN(0x118, 0xf)
+  SOM_DPP_MIN(0x142, 0xa)
+  SOM_DPP_MIN(0x143, 0xc)
+#undef SOM_DPP_MIN
+  return static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(x), 63));
+}
+
+// Distances, argmin (or the two smallest) and key merge of a wave's DW
+// documents over its slice.  Per document the lane's best neuron is reduced
+// over the wave as ordered distance bits; the lowest lane that holds the
+// minimum gives the lowest index (a lane's neurons ascend, and lanes do; columns
+// past the last neuron are +inf, behind every neuron).  Lane s then holds
+// document s's key, and one vector compare filters the atomics: a stale read of
+// the stored key only lets a useless update through, as keys only fall.
+template <int DW, int NPL, bool TOP2>
+__device__ __forceinline__ void list_epilogue(const SearchArgs& a, const ListAcc<DW, NPL>& acc, int64_t p0, int64_t n0,
+                                              int lane) {
+  if (p0 >= a.B) return;   // (documents past the last are reduced with the others, and not stored)
+  float nrm[NPL];
+#pragma unroll
+  for (int q = 0; q < NPL; ++q) {
+    const int64_t j = n0 + lane * NPL + q;
+    nrm[q] = j < a.N ? a.norms[j] : __builtin_inff();
+  }
+  const int64_t p = p0 + lane;
+  const bool mine = lane < DW && p < a.B;
+  float nnz = 0.f;
+  if (mine) {
+    const int64_t d = a.perm ? static_cast<int64_t>(a.perm[p]) : p;
+    nnz = static_cast<float>(a.indptr[d + 1] - a.indptr[d]);
+  }
+  int m1 = -1, j1 = 0, m2 = -1, j2 = 0;
+#pragma unroll
+  for (int s = 0; s < DW; ++s) {
+    const float nn = __uint_as_float(
+        static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(__float_as_uint(nnz)), s)));
+    float d1 = 0.f, d2 = __builtin_inff();   // the lane's best, and second best
+    uint32_t q1 = 0, q2 = 0;
+#pragma unroll
+    for (int q = 0; q < NPL; ++q) {
+      const float d = fmaf(-2.f, acc.p[q][s], nn + nrm[q]);
+      const bool lt1 = q == 0 || d < d1;     // ascending neurons: strict < keeps the lowest
+      if (TOP2) {
+        const bool lt2 = q == 1 || d < d2;
+        if (q > 0) {
+          d2 = lt1 ? d1 : (lt2 ? d : d2);
+          q2 = lt1 ? q1 : (lt2 ? static_cast<uint32_t>(q) : q2);
+        }
+      }
+      q1 = lt1 ? static_cast<uint32_t>(q) : q1;
+      d1 = lt1 ? d : d1;
+    }
+    const uint32_t b1 = ordered_bits(d1);
+    const uint32_t m = wave_min_u32(b1);
+    const int l = __builtin_ctzll(__ballot(b1 == m));   // some lane holds the minimum
+    const int j = static_cast<int>(n0) + l * NPL + __builtin_amdgcn_readlane(static_cast<int>(q1), l);
+    m1 = lane == s ? static_cast<int>(m) : m1;
+    j1 = lane == s ? j : j1;
+    if (TOP2) {
+      const uint32_t c = lane == l ? ordered_bits(d2) : b1;
+      const uint32_t cq = lane == l ? q2 : q1;
+      const uint32_t mm = wave_min_u32(c);
+      const int l2 = __builtin_ctzll(__ballot(c == mm));
+      const int jj = static_cast<int>(n0) + l2 * NPL + __builtin_amdgcn_readlane(static_cast<int>(cq), l2);
+      m2 = lane == s ? static_cast<int>(mm) : m2;
+      j2 = lane == s ? jj : j2;
+    }
+  }
+  if (!mine) return;
+  const uint64_t k1 = (static_cast<uint64_t>(static_cast<uint32_t>(m1)) << 32) | static_cast<uint32_t>(j1);
+  uint64_t* kb = a.keys + p;
+  if (!TOP2) {
+    if (k1 < *kb) atomicMin(reinterpret_cast<unsigned long long*>(kb), static_cast<unsigned long long>(k1));
+    return;
+  }
+  // a slice of one neuron has no second best
+  const uint64_t k2 = a.N - n0 < 2 ? kNoKey
+                                   : (static_cast<uint64_t>(static_cast<uint32_t>(m2)) << 32) | static_cast<uint32_t>(j2);
+  const uint64_t displaced = k1 < *kb ? top2_displaced(kb, k1) : k1;
+  const uint64_t cand = displaced < k2 ? displaced : k2;
+  uint64_t* ks = a.keys2 + p;
+  if (cand < *ks) atomicMin(reinterpret_cast<unsigned long long*>(ks), static_cast<unsigned long long>(cand));
+}
+
+// Waves per SIMD the registers must allow: the four that two workgroups per CU
+// make, except where an fp16 codebook is searched with a plan made for fp32 (128
+// accumulators per lane).
+template <typename WT, int DW>
+constexpr int list_min_waves() {
+  return sizeof(WT) == 2 && DW == 32 ? 2 : 4;
+}
+
+// WIDE: codebook rows of 4 GB and more.
+template <typename WT, int DW, bool TOP2, bool WIDE>
+__global__ void __launch_bounds__(kListWaves * 64) __attribute__((amdgpu_waves_per_eu(list_min_waves<WT, DW>())))
+k_search_list(SearchArgs a) {
+  constexpr int E = Storage<WT>::kE;                               // elements per 128-bit load
+  constexpr int NPL = kListRowBytes / 64 / static_cast<int>(sizeof(WT));  // neurons per lane
+  constexpr int64_t WN = 64 * NPL;                                 // neurons per slice
+  constexpr int S = kListWaves, R = kListRows;
+  constexpr uint32_t kSlot = R * kListRowBytes;
+  static_assert(R == 8 * S && kListRowBytes == 512 && kSlot == 0x8000, "four two-row loads per wave and stage");
+  // the kernel's only LDS object, at LDS address 0: entry addresses are formed
+  // by or-ing a row's offset into the slot's base
+  __shared__ __attribute__((aligned(1024))) unsigned char ring[2 * R * kListRowBytes];
+
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  // XCD-contiguous tile ranges, slice-major (see k_search)
+  const uint32_t per_xcd = gridDim.x / kXcds;
+  const int64_t t = static_cast<int64_t>(blockIdx.x % kXcds) * per_xcd + blockIdx.x / kXcds;
+  if (t >= a.ntiles) return;  // whole workgroup: no barrier is skipped by part of it
+  const int64_t n0 = (a.slice_base + blockIdx.y) * WN;
+
+  ListAcc<DW, NPL> acc;
+#pragma unroll
+  for (int q = 0; q < NPL; ++q)
+#pragma unroll
+    for (int s = 0; s < DW; ++s) acc.p[q][s] = 0.f;
+
+  // lane's 16 bytes of a row: piece lane % 32; lanes past the last neuron
+  // re-read the last 128-bit group holding one, so no load leaves
+  // [0, round_up(N, E)) of its row
+  const int64_t o = E * (lane & 31);
+  const int64_t nv = (a.N + E - 1) / E * E;
+  const char* __restrict__ Wl = reinterpret_cast<const char*>(static_cast<const WT*>(a.W) + n0 +
+                                                              (n0 + o < nv ? o : nv - E - n0));
+  const uint64_t ldw_b = static_cast<uint64_t>(a.ldw) * sizeof(WT);
+  typedef const __attribute__((address_space(4))) uint32_t* const_u32;
+  typedef const __attribute__((address_space(4))) int32_t* const_i32;
+  typedef const __attribute__((address_space(4))) char* const_char;
+  const int64_t cap0 = ((const_i32)a.tile_offset)[t];
+  const int32_t nst = ((const_i32)a.tile_count)[t];   // stages
+  // unit offsets of the tile's lists, stage by stage: list (q, w) holds units
+  // pt[q * S + w] .. pt[q * S + w + 1]
+  const const_u32 pt = (const_u32)(a.list_start + cap0 * S + t);
+  const unsigned char* data = a.list_data + cap0 * kListCapBytes;
+  const const_char lists = (const_char)(data + nst * (R * 4));
+
+  if (nst > 0) {
+    // Rotated sweep: the tile's phase, as in kernel 3 (the nonzeros of
+    // the XCD's earlier tiles over a.phase_wgs tiles' mean, mod 1), then the
+    // stage that holds this fraction of the tile's own work, a stage counting
+    // as kListStageWork entries beside those it holds.
+    int32_t q = 0;
+    if (a.rotate && nst > 1) {
+      const int64_t first = static_cast<int64_t>(blockIdx.x % kXcds) * per_xcd;
+      const int64_t end = first + per_xcd < a.ntiles ? first + per_xcd : a.ntiles;
+      const uint64_t o_first = static_cast<uint32_t>(((const_i32)a.tile_offset)[first]);
+      const uint64_t work = static_cast<uint32_t>(((const_i32)a.tile_offset)[end]) - o_first;  // > 0
+      const uint64_t den = static_cast<uint64_t>(a.phase_wgs) * work;
+      const uint64_t num = (static_cast<uint64_t>(cap0) - o_first) * static_cast<uint64_t>(end - first) % den;
+      const uint64_t ph = (num << 20) / den;                       // phase in 2^-20
+      const uint64_t total = 4ull * pt[nst * S] + static_cast<uint64_t>(kListStageWork) * nst;
+      const uint64_t target = (ph * total) >> 20;
+      int32_t hi = nst;                                            // largest q whose work is at most the target
+      while (hi - q > 1) {
+        const int32_t mid = (q + hi) >> 1;
+        if (4ull * pt[mid * S] + static_cast<uint64_t>(kListStageWork) * mid <= target)
+          q = mid;
+        else
+          hi = mid;
+      }
+      q = __builtin_amdgcn_readfirstlane(q);
+    }
+    const uint32_t ring0 = lds_offset(ring);
+    const uint32_t wbase = ring0 + static_cast<uint32_t>(wave * 4096);
+    // this lane's half loads rows wave*8 + 4*half + i of a stage, i = 0..3,
+    // into slot rows (wave*4 + i)*2 + half (the plan's entries hold slot rows)
+    const char* __restrict__ ids = reinterpret_cast<const char*>(data);
+    const uint32_t idl = static_cast<uint32_t>(wave * 32 + (lane >> 5) * 16);
+    constexpr uint32_t kStarts = S * 4;   // bytes of list starts per stage
+    auto load_ids = [&](uint32_t sb) { return *reinterpret_cast<const i32x4v*>(ids + (sb * (R * 4 / kStarts) + idl)); };
+    const uint32_t ldw_lo = static_cast<uint32_t>(ldw_b);
+    auto issue = [&](const i32x4v& id, uint32_t slot) {
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+        dma_b128(Wl + static_cast<uint64_t>(static_cast<uint32_t>(id[i])) * (WIDE ? ldw_b : static_cast<uint64_t>(ldw_lo)),
+                 wbase + slot + static_cast<uint32_t>(i * 1024));
+    };
+    typedef uint32_t u32x2v __attribute__((ext_vector_type(2)));
+    const const_char starts = (const_char)(pt + wave);
+    auto load_range = [&](uint32_t sb) { return *(const __attribute__((address_space(4))) u32x2v*)(starts + sb); };
+    const uint32_t end = static_cast<uint32_t>(nst) * kStarts;
+    auto after = [&](uint32_t sb) { return sb + kStarts == end ? 0u : sb + kStarts; };
+
+    // offsets in the list starts: the next stage's, and the one after
+    uint32_t sb = static_cast<uint32_t>(q) * kStarts;
+    i32x4v id = load_ids(sb);
+    issue(id, 0);
+    u32x2v cur = load_range(sb);
+    u32x8v set = *(const __attribute__((address_space(4))) u32x8v*)(lists + cur.x * 8u);
+    sb = after(sb);
+    id = load_ids(sb);
+    u32x2v next = load_range(sb);
+    const uint32_t vl0 = ring0 | static_cast<uint32_t>(lane * 8);
+    const uint32_t vm = 0xfe00u;
+    const uint64_t lb = reinterpret_cast<uint64_t>((const char*)lists);
+    // `more`: a stage follows (its loads are issued); `none`: no stage at all,
+    // the filler of an odd count
+    auto step = [&](auto odd, bool more, bool none) {
+      constexpr bool ODD = decltype(odd)::value;
+      constexpr uint32_t slot = ODD ? kSlot : 0;
+      // this wave's rows of the stage (and its ids of the next) have landed;
+      // the builtin (vmcnt(0), the other counters untouched) tells the compiler
+      // so about the ids, whose own wait would otherwise fall after the issue
+      // below and drain it
+      __builtin_amdgcn_s_waitcnt(0x0f70);
+      lds_barrier();  // the stage is visible to all waves; every wave is done with the stage before
+      if (more) issue(id, kSlot - slot);
+      sb = after(sb);
+      id = load_ids(sb);
+      const u32x2v next2 = load_range(sb);
+      const uint32_t n = none ? ~0u : cur.y - cur.x - 1u;
+      set = add_list<ODD>(acc, set, lb, cur.x * 8u, next.x * 8u, n, vl0 | slot, vm);
+      cur = next;
+      next = next2;
+    };
+    for (int32_t left = nst; left > 0; left -= 2) {   // stages from this one on
+      step(std::false_type{}, left > 1, false);
+      step(std::true_type{}, left > 2, left == 1);
+    }
+  }
+  list_epilogue<DW, NPL, TOP2>(a, acc, t * (S * DW) + wave * DW, n0, lane);
+}
+
+template <typename WT, int DW>
+hipError_t launch_list(const SearchArgs& a, hipStream_t stream) {
+  // grid.y holds at most 65,535 slices: wider maps take several launches
+  constexpr int64_t WN = 64 * kListRowBytes / 64 / static_cast<int64_t>(sizeof(WT));
+  const int64_t slices = (a.N + WN - 1) / WN;
+  const bool wide = static_cast<uint64_t>(a.ldw) * sizeof(WT) >> 32;
+  SearchArgs b = a;
+  b.phase_wgs = kListPhaseWgs;
+  for (int64_t c = 0; c < slices; c += 65535) {
+    b.slice_base = c;
+    const dim3 grid(static_cast<uint32_t>((a.ntiles + kXcds - 1) / kXcds * kXcds),
+                    static_cast<uint32_t>(slices - c < 65535 ? slices - c : 65535));
+    if (wide && a.keys2)
+      hipLaunchKernelGGL((k_search_list<WT, DW, true, true>), grid, dim3(kListWaves * 64), 0, stream, b);
+    else if (wide)
+      hipLaunchKernelGGL((k_search_list<WT, DW, false, true>), grid, dim3(kListWaves * 64), 0, stream, b);
+    else if (a.keys2)
+      hipLaunchKernelGGL((k_search_list<WT, DW, true, false>), grid, dim3(kListWaves * 64), 0, stream, b);
+    else
+      hipLaunchKernelGGL((k_search_list<WT, DW, false, false>), grid, dim3(kListWaves * 64), 0, stream, b);
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+  }
+  return hipSuccess;
+}
+
+}  // namespace
+}  // namespace som

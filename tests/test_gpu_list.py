@@ -1,0 +1,104 @@
+"""GPU checks of the automatic launch's list form (tiles of 256 documents for
+fp32, 128 for fp16; per-wave entry lists) at the sizes where it can go wrong:
+the batch size it starts at and ragged last tiles, unions of one stage and of
+one row more, documents with no feature and with more than two 64-lane reads of
+them, maps around the slice width, the largest vocabulary it takes, rows of 4 GB
+and more, and plans searched with the other storage type.
+
+The codebooks are dyadic (W in {0, 1/4, 1/2, 3/4}), so every fp32 sum is exact
+and every order of summation must give kernel 1's bits; kernel 1 faces the
+oracle in the parity tests.  On a random codebook the ascending sweep must give
+kernel 1's bits as well."""
+
+import numpy as np
+import pytest
+
+torch = pytest.importorskip("torch")
+pytestmark = pytest.mark.gpu
+
+if torch.cuda.is_available():
+    import paper_2609_05138_amd as som
+else:  # collected on CPU-only machines, never run there
+    som = None
+
+DEV = "cuda:0"
+MIN_DOCS = {np.float32: 1536, np.float16: 1024}   # batches from which the list form is taken
+
+
+def _docs(rng, B, F):
+    """CSR batch: mostly short documents over frequent ids, every 37th empty,
+    every 101st with as many features as F allows up to 300."""
+    n = np.minimum(rng.poisson(min(12, F / 2), B), F)
+    n[::37] = 0
+    n[1::101] = min(F, 300)
+    rows = []
+    for k in n:
+        ids = rng.choice(F, k, replace=False) if k > F // 4 else np.unique(
+            np.minimum((F * rng.random(k) ** 3).astype(np.int64), F - 1))
+        rows.append(np.sort(ids))
+    indptr = np.concatenate([[0], np.cumsum([len(r) for r in rows])])
+    return (torch.from_numpy(indptr.astype(np.int32)).to(DEV),
+            torch.from_numpy(np.concatenate(rows).astype(np.int32)).to(DEV))
+
+
+def _book(rng, F, N, dtype, ldw=None, dyadic=True):
+    W = torch.zeros((F, ldw or som.som_codebook_ldw(N)), dtype=torch.float16 if dtype == np.float16 else torch.float32,
+                    device=DEV)
+    v = rng.integers(0, 4, (F, N)) / 4 if dyadic else rng.random((F, N), dtype=np.float32)
+    W[:, :N] = torch.from_numpy(v.astype(dtype)).to(DEV)
+    return W, som.som_codebook_norms(W, N=N)
+
+
+def _equal(a, b):
+    return all(torch.equal(x, y) for x, y in zip(a, b))
+
+
+@pytest.mark.parametrize("dtype", [np.float32, np.float16])
+@pytest.mark.parametrize("extra,F,N", [(-1, 300, 200), (0, 64, 128), (1, 65, 127), (255, 2000, 129), (256, 64, 1),
+                                       (300, 65536, 300), (130, 5000, 513), (1000, 1, 2)])
+def test_list_form_matches_kernel_1(dtype, extra, F, N):
+    rng = np.random.default_rng(F * 1000 + N)
+    B = MIN_DOCS[dtype] + extra
+    ip, ix = _docs(rng, B, F)
+    perm = som.som_cluster_order(ip, ix, F)
+    W, norms = _book(rng, F, N, dtype)
+    for p in (None, perm):
+        want = som.som_bmu_search_top2(W, norms, ip, ix, N=N, perm=p, kernel=1, sweep=1)
+        for sweep in (0, 1):
+            got = som.som_bmu_search_top2(W, norms, ip, ix, N=N, perm=p, sweep=sweep)
+            assert _equal(got, want), (sweep, p is None)
+            assert _equal(som.som_bmu_search(W, norms, ip, ix, N=N, perm=p, sweep=sweep), want[:2]), sweep
+
+
+@pytest.mark.parametrize("dtype", [np.float32, np.float16])
+def test_list_form_ascending_bits_and_reuse_of_a_plan(dtype):
+    rng = np.random.default_rng(7)
+    F, N, B = 3000, 1000, 6000
+    ip, ix = _docs(rng, B, F)
+    perm = som.som_cluster_order(ip, ix, F)
+    W, norms = _book(rng, F, N, dtype, dyadic=False)
+    want = som.som_bmu_search_top2(W, norms, ip, ix, N=N, perm=perm, kernel=1, sweep=1)
+    assert _equal(som.som_bmu_search_top2(W, norms, ip, ix, N=N, perm=perm, sweep=1), want)
+    # a plan made for either storage type serves both, with the same bits
+    other = W.to(torch.float16 if dtype == np.float32 else torch.float32)
+    other_norms = som.som_codebook_norms(other, N=N)
+    for storage in (0, 1):
+        for sweep in (0, 1):
+            plan = som.som_plan(ip, ix, F, perm=perm, storage=storage, sweep=sweep)
+            mine = som.som_bmu_search_top2_planned(W, norms, ip, plan, N=N)
+            assert _equal(som.som_bmu_search_planned(W, norms, ip, plan, N=N), mine[:2])
+            if sweep == 1:
+                assert _equal(mine, want), storage
+            half = som.som_bmu_search_top2_planned(other, other_norms, ip, plan, N=N)
+            if dtype == np.float16:      # the widened codebook holds the same values
+                assert _equal(half, mine), (storage, sweep)
+
+
+def test_list_form_rows_of_4_gib():
+    rng = np.random.default_rng(11)
+    F, N, B = 2, 300, 1700
+    ip, ix = _docs(rng, B, F)
+    W, norms = _book(rng, F, N, np.float32, ldw=(1 << 30) + 64)
+    want = som.som_bmu_search_top2(W, norms, ip, ix, N=N, kernel=1, sweep=1)
+    assert _equal(som.som_bmu_search_top2(W, norms, ip, ix, N=N), want)
+    assert _equal(som.som_bmu_search(W, norms, ip, ix, N=N), want[:2])
