@@ -66,7 +66,9 @@ typedef enum som_status {
  * batches of 1,536 documents and more (fp16: 1,024) over at most 65,536
  * features take the list form of kernel 3, whose plan holds, per tile of 256
  * documents (fp16: 128) and wave, lists of the (row, document) memberships; it
- * lives in the bytes of the kernel it stands in for.  Otherwise: for an fp32
+ * lives in the bytes of the kernel it stands in for; smaller batches (fp16:
+ * fewer than 768 documents) take kernel 1 with two-document tiles.  Otherwise
+ * (a knob given, a larger vocabulary, fp16 batches between): for an fp32
  * codebook kernel 3 with 64-document super-tiles and the document-major
  * dispatch; for fp16, or when a knob only kernel 1 has is set (tile_docs of 32
  * or less, lane_neurons, group_tiles), kernel 1 with tiles of 16 documents for

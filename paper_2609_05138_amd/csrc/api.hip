@@ -93,6 +93,25 @@ struct Plan {
 // 256^2 map and fp16 codebooks were neutral or slower).
 constexpr int64_t kGroupTilesMinN = 131072;
 
+// No knob names a kernel or a geometry (the automatic launch).
+bool no_geometry(const som_bmu_opts& o) {
+  return !o.kernel && !o.tile_docs && !o.lane_neurons && !o.group_tiles && !o.mask_mode && !o.slice_neurons &&
+         o.schedule != 2 && !o.neuron_chunk;
+}
+
+// Small batches: the automatic launch takes kernel 1 with two-document tiles,
+// one wave each, which spread a batch over the device where the shared-union
+// kernels would leave most of it idle and each of their workgroups a long chain
+// of stages; its plan is short too.  Whole search calls, F = 20,000, fp32, in
+// us (kernel 3 / this): 16 documents on 128^2 151 / 51, 256 on 32^2 260 / 50,
+// 256 on 128^2 353 / 154, 1,024 on 128^2 480 / 456 and on 256^2 1,247 / 1,222;
+// 2,048 on 128^2 737 / 788 (the list form: 532).  fp16 (kernel 1 with
+// eight-document tiles / this): 16 on 128^2 108 / 52, 256 on 128^2 124 / 96,
+// 512 on 256^2 432 / 401 and on 128^2 158 / 162, 1,024 on 128^2 234 / 284 (the
+// list form: 198).  The line depends on the batch only, as a plan does.
+constexpr int64_t kSmallDocsF32 = 1536, kSmallDocsF16 = 768;
+constexpr int kSmallTileDocs = 2;
+
 // `weights` is the storage type of the codebook searched (it fixes the load
 // width K); `auto_weights` the one the automatic tile size is chosen for:
 // the entry point's own type when it plans internally, opts->storage for
@@ -113,13 +132,14 @@ som_status make_plan(int64_t N, int64_t B, const som_bmu_opts* opts, Plan* p, in
   // topic workload; kernel 1 for fp16 (8-document tiles, measured faster
   // there) and whenever a knob only kernel 1 has is given
   const bool k1_knob = (o.tile_docs > 0 && o.tile_docs <= 32) || o.lane_neurons || o.group_tiles;
-  const int kernel = o.kernel ? o.kernel : ((auto16 || k1_knob) ? 1 : 3);
+  const bool small = no_geometry(o) && B < (auto16 ? kSmallDocsF16 : kSmallDocsF32);
+  const int kernel = o.kernel ? o.kernel : ((auto16 || k1_knob || small) ? 1 : 3);
   p->kernel = kernel;
   if (kernel == 1) {
     // automatic tile size: 16 documents for fp32 (about 5% faster than 8 on
     // the 512^2 map), 8 for fp16 (whose 512-neuron slices leave fewer
     // registers for accumulators)
-    const int T = o.tile_docs ? o.tile_docs : (auto16 ? 8 : 16);
+    const int T = o.tile_docs ? o.tile_docs : (small ? kSmallTileDocs : (auto16 ? 8 : 16));
     if (T != 1 && T != 2 && T != 4 && T != 8 && T != 16 && T != 32)
       return fail(SOM_ERR_INVALID_ARG, "opts->tile_docs must be 0, 1, 2, 4, 8, 16 or 32");
     if (f16 && T == 32) return fail(SOM_ERR_INVALID_ARG, "opts->tile_docs 32 is not available for an fp16 codebook");
@@ -270,14 +290,12 @@ PlanLayout plan_layout(const Plan& p, int64_t nnz) {
 // depends on the batch and F only, not on N, so that a plan serves any codebook
 // and column ranges of one compose exactly.  Any kernel or geometry knob keeps
 // the named kernel.
-constexpr int64_t kListMinDocsF32 = 1536, kListMinDocsF16 = 1024;
+constexpr int64_t kListMinDocsF32 = kSmallDocsF32, kListMinDocsF16 = 1024;
 
 void choose_lists(int64_t F, int64_t B, int64_t nnz, const som_bmu_opts* opts, int auto_weights, Plan* p) {
   som_bmu_opts o{};
   if (opts) o = *opts;
-  if (o.kernel || o.tile_docs || o.lane_neurons || o.group_tiles || o.mask_mode || o.slice_neurons ||
-      o.schedule == 2 || o.neuron_chunk)
-    return;
+  if (!no_geometry(o)) return;
   const bool f16 = auto_weights == som::kWeightsF16;
   if (F > som::kListMaxF || B < (f16 ? kListMinDocsF16 : kListMinDocsF32)) return;
   const int docs = f16 ? 16 : 32;

@@ -94,6 +94,22 @@ def test_list_form_ascending_bits_and_reuse_of_a_plan(dtype):
                 assert _equal(half, mine), (storage, sweep)
 
 
+@pytest.mark.parametrize("dtype", [np.float32, np.float16])
+@pytest.mark.parametrize("B", [1, 2, 3, 700, 767, 768, 1023])
+def test_small_batches_match_kernel_1(dtype, B):
+    # below the list form: two-document tiles of kernel 1 (fp16 up to 767)
+    rng = np.random.default_rng(B)
+    F, N = 900, 700
+    ip, ix = _docs(rng, B, F)
+    W, norms = _book(rng, F, N, dtype)
+    want = som.som_bmu_search_top2(W, norms, ip, ix, N=N, kernel=1, tile_docs=8, sweep=1)
+    assert _equal(som.som_bmu_search_top2(W, norms, ip, ix, N=N), want)
+    plan = som.som_plan(ip, ix, F, storage=1 if dtype == np.float16 else 0)
+    assert _equal(som.som_bmu_search_planned(W, norms, ip, plan, N=N), want[:2])
+    if dtype == np.float32:
+        assert _equal(som.som.som_bmu_search_noalloc(W, norms, ip, ix, N=N), want[:2])
+
+
 def test_list_form_rows_of_4_gib():
     rng = np.random.default_rng(11)
     F, N, B = 2, 300, 1700
