@@ -9,9 +9,9 @@
 //                 count[bmu] += 1, as uint32 atomics (exact, order-free)
 //  k_taps         g[k] = exp(-k^2 / (2 sigma^2)) for k = 0..R, in fp64, rounded
 //                 to fp32 once
-//  k_blur_rows    one grid row of one feature per workgroup, staged in LDS:
+//  k_blur_rows    some grid rows of one feature per workgroup, staged in LDS:
 //                 t[r][c] = sum_{k=-R..R} g[|k|] acc[r][c+k]  (fixed tap order)
-//  k_blur_cols    a strip of 32 columns of one feature per workgroup, staged
+//  k_blur_cols    a strip of 32 or 16 columns of one feature per workgroup, staged
 //                 in LDS: v[r][c] = sum_k g[|k|] t[r+k][c]; then either the
 //                 blurred counts (den) or the write-back W = v / den where
 //                 den > 0 (other units keep their weights)
@@ -52,38 +52,159 @@ __global__ void k_taps(double sigma, int R, float* __restrict__ g) {
   g[k] = sigma > 0 ? static_cast<float>(exp(-static_cast<double>(k) * k / (2.0 * sigma * sigma))) : 1.f;
 }
 
-// in: plane p of the input (uint32 accumulators or fp32), rows x cols with
-// row stride `cols` inside a plane of stride ld_in; out: fp32 plane of
-// stride ld_out.  Grid (rows, planes): rows fastest, so that concurrent
-// workgroups spread over one plane rather than hitting the same offset of
-// planes a power-of-two stride apart (the same memory channels).
-template <typename IN>
-__global__ void __launch_bounds__(256)
-k_blur_rows(const IN* __restrict__ in, int64_t ld_in, float* __restrict__ out, int64_t ld_out, int cols, int R,
-            const float* __restrict__ g) {
-  extern __shared__ float row[];
-  const int64_t p = blockIdx.y;
-  const int r = blockIdx.x;
-  const IN* src = in + p * ld_in + static_cast<int64_t>(r) * cols;
-  for (int c = threadIdx.x; c < cols; c += blockDim.x) row[c] = static_cast<float>(src[c]);
-  __syncthreads();
-  float* dst = out + p * ld_out + static_cast<int64_t>(r) * cols;
-  for (int c = threadIdx.x; c < cols; c += blockDim.x) {
-    const int lo = c - R < 0 ? -c : -R;
-    const int hi = c + R >= cols ? cols - 1 - c : R;
-    float s = 0.f;
-    for (int k = lo; k <= hi; ++k) s = fmaf(g[k < 0 ? -k : k], row[c + k], s);
-    dst[c] = s;
+// Both blur passes give each thread eight neighbouring outputs: as the taps are
+// walked, one new cell enters the thread's window per tap and feeds eight
+// multiply-adds, so an output costs an eighth of an LDS read per tap.  (Reading
+// each output's own window, tap by tap, bound both passes on the LDS.)  Whole
+// calls, F = 4,000, fp32 weights, before and now: 128^2 map, R = 48 2.80 and
+// 0.57 ms; 512^2, R = 17 25.4 and 9.1, R = 48 44.1 and 9.7, R = 192 176 and 23.4.
+// What bounds them now: the loads of a row group or strip, which its arithmetic
+// waits for, and at R = 192 the multiply-adds.  Cells outside the grid are zero
+// in LDS: their terms leave the sums unchanged, which otherwise take the same
+// terms in the same order, k = -R..R.
+constexpr int kOut = 8;   // outputs per thread
+
+// One step of the window: output i's tap k reads cell i + k of the window's
+// start; WIN holds kOut cells, rotated by the unrolled loop.
+template <typename READ>
+__device__ __forceinline__ void blur_window(const float* taps, int n, float (&out)[kOut], READ read) {
+  // taps[0..n-1]; out[i] = sum_j taps[j] * read(i + j), j ascending
+  float w[kOut];
+#pragma unroll
+  for (int i = 0; i < kOut; ++i) {
+    w[i] = read(i);
+    out[i] = 0.f;
+  }
+  int j = 0;
+  for (; j + kOut <= n; j += kOut) {
+#pragma unroll
+    for (int u = 0; u < kOut; ++u) {
+      const float g = taps[j + u];
+#pragma unroll
+      for (int i = 0; i < kOut; ++i) out[i] = fmaf(g, w[(u + i) % kOut], out[i]);
+      w[u] = read(j + u + kOut);
+    }
+  }
+  for (; j < n; ++j) {   // fewer than kOut taps: the window shifts by moves
+    const float g = taps[j];
+#pragma unroll
+    for (int i = 0; i < kOut; ++i) out[i] = fmaf(g, w[i], out[i]);
+#pragma unroll
+    for (int i = 0; i + 1 < kOut; ++i) w[i] = w[i + 1];
+    w[kOut - 1] = read(j + kOut);
   }
 }
 
-// MODE 0: den[j] = v (one plane); MODE 1: write-back into the codebook.
-// Grid (strips, planes), strips fastest (see k_blur_rows).
+// LDS position of cell c of a row: one float of padding per kOut keeps the
+// threads' windows (kOut cells apart) on different banks.
+__device__ __host__ __forceinline__ int row_pos(int c) { return c + c / kOut; }
+
+// LDS floats of one padded row: Re cells each side, the columns rounded up to
+// whole threads, and the cells the last window reads ahead.
+__host__ __device__ inline int blur_row_floats(int cols, int Re) {
+  return row_pos((cols + kOut - 1) / kOut * kOut + 2 * Re + kOut) + 1;
+}
+
+// Row pass.  in: plane p of the input (uint32 accumulators), rows x cols with
+// row stride `cols` inside a plane of stride ld_in; out: fp32 plane of stride
+// ld_out.  A workgroup takes `per` rows of one plane; grid (row groups, planes),
+// row groups fastest, so that concurrent workgroups spread over one plane rather
+// than hitting the same offset of planes a power-of-two stride apart (the same
+// memory channels).  Re = min(R, cols - 1).
+template <typename IN>
+__global__ void __launch_bounds__(256)
+k_blur_rows(const IN* __restrict__ in, int64_t ld_in, float* __restrict__ out, int64_t ld_out, int rows, int cols,
+            int Re, int per, const float* __restrict__ g) {
+  extern __shared__ float lds[];
+  float* taps = lds;                            // [2 Re + 1]
+  const int stride = blur_row_floats(cols, Re);
+  float* cells = lds + (2 * Re + 1);            // [per][stride]
+  const int64_t p = blockIdx.y;
+  const int r0 = blockIdx.x * per;
+  const int nr = rows - r0 < per ? rows - r0 : per;
+  for (int j = threadIdx.x; j < 2 * Re + 1; j += blockDim.x) taps[j] = g[j < Re ? Re - j : j - Re];
+  for (int i = threadIdx.x; i < nr * stride; i += blockDim.x) cells[i] = 0.f;
+  __syncthreads();
+  const IN* src = in + p * ld_in + static_cast<int64_t>(r0) * cols;
+  for (int i = threadIdx.x; i < nr * cols; i += blockDim.x) {
+    const int r = i / cols, c = i - r * cols;
+    cells[r * stride + row_pos(c + Re)] = static_cast<float>(src[i]);
+  }
+  __syncthreads();
+  const int groups = (cols + kOut - 1) / kOut;   // threads per row
+  float* dst = out + p * ld_out + static_cast<int64_t>(r0) * cols;
+  for (int i = threadIdx.x; i < nr * groups; i += blockDim.x) {
+    const int r = i / groups, c = (i - r * groups) * kOut;
+    const float* row = cells + r * stride;
+    float v[kOut];
+    blur_window(taps, 2 * Re + 1, v, [&](int k) { return row[row_pos(c + k)]; });
+#pragma unroll
+    for (int k = 0; k < kOut; ++k)
+      if (c + k < cols) dst[r * cols + c + k] = v[k];
+  }
+}
+
+// Column pass.  MODE 0: den[j] = v (one plane); MODE 1: write-back into the
+// codebook.  A workgroup takes a strip of STRIP columns of one plane, all rows
+// and Re zero rows each side in LDS, STRIP + STRIP / 8 floats apart, which puts
+// the wave's 64 / STRIP row groups (kOut rows apart) on different banks.  Grid
+// (strips, planes), strips fastest (see k_blur_rows).  Re = min(R, rows - 1).
+// 512 threads: 256 left too few loads in flight beside an 80 KB strip (512^2, R =
+// 17: 12.0 ms per call against 9.1)
+constexpr int kColThreads = 512;
+
+template <int STRIP>
+__host__ __device__ constexpr int blur_col_stride() {
+  return STRIP + STRIP / 8;
+}
+
+template <typename WT, int MODE, int STRIP>
+__global__ void __launch_bounds__(kColThreads)
+k_blur_cols(const float* __restrict__ t, int64_t ld_t, int rows, int cols, int Re, const float* __restrict__ g,
+            float* __restrict__ den_out, const float* __restrict__ den, WT* __restrict__ W, int64_t ldw) {
+  extern __shared__ float lds[];
+  constexpr int kStride = blur_col_stride<STRIP>();
+  constexpr int kGroups = kColThreads / STRIP;           // row groups in flight
+  float* taps = lds;                             // [2 Re + 1]
+  float* strip = lds + (2 * Re + 1);             // [rows + 2 Re + 2 kOut][kStride]
+  const int64_t p = blockIdx.y;
+  const int cx = threadIdx.x % STRIP;
+  const int c = blockIdx.x * STRIP + cx;
+  const int ry = threadIdx.x / STRIP;
+  const float* src = t + p * ld_t;
+  for (int j = threadIdx.x; j < 2 * Re + 1; j += kColThreads) taps[j] = g[j < Re ? Re - j : j - Re];
+  for (int r = ry; r < rows + 2 * Re + 2 * kOut; r += kGroups) {
+    const int rr = r - Re;
+    strip[r * kStride + cx] = rr >= 0 && rr < rows && c < cols ? src[static_cast<int64_t>(rr) * cols + c] : 0.f;
+  }
+  __syncthreads();
+  if (c >= cols) return;
+  for (int r0 = ry * kOut; r0 < rows; r0 += kGroups * kOut) {
+    const float* col = strip + r0 * kStride + cx;
+    float v[kOut];
+    blur_window(taps, 2 * Re + 1, v, [&](int k) { return col[k * kStride]; });
+#pragma unroll
+    for (int k = 0; k < kOut; ++k) {
+      if (r0 + k >= rows) break;
+      const int64_t j = static_cast<int64_t>(r0 + k) * cols + c;
+      if (MODE == 0) {
+        den_out[j] = v[k];
+      } else {
+        const float dj = den[j];
+        if (dj > 0.f) W[p * ldw + j] = static_cast<WT>(v[k] / dj);
+      }
+    }
+  }
+}
+
+// The column pass of maps and radii whose strip with its zero rows exceeds the
+// LDS: 32 columns, only the grid's rows in LDS, each output's window tap by tap.
 template <typename WT, int MODE>
 __global__ void __launch_bounds__(256)
-k_blur_cols(const float* __restrict__ t, int64_t ld_t, int rows, int cols, int R, const float* __restrict__ g,
-            float* __restrict__ den_out, const float* __restrict__ den, WT* __restrict__ W, int64_t ldw) {
-  extern __shared__ float strip[];  // [rows][kStrip]
+k_blur_cols_tall(const float* __restrict__ t, int64_t ld_t, int rows, int cols, int R, const float* __restrict__ g,
+                 float* __restrict__ den_out, const float* __restrict__ den, WT* __restrict__ W, int64_t ldw) {
+  extern __shared__ float lds[];
+  float* strip = lds;  // [rows][kStrip]
   const int64_t p = blockIdx.y;
   const int c0 = blockIdx.x * kStrip;
   const int cx = threadIdx.x % kStrip;
@@ -107,6 +228,63 @@ k_blur_cols(const float* __restrict__ t, int64_t ld_t, int rows, int cols, int R
       if (dj > 0.f) W[p * ldw + j] = static_cast<WT>(s / dj);
     }
   }
+}
+
+constexpr size_t kLdsBytes = 160 * 1024;   // per workgroup
+
+template <typename F>
+hipError_t allow_lds(F* kernel, size_t bytes) {
+  return hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize,
+                             static_cast<int>(bytes));
+}
+
+hipError_t launch_blur_rows(const uint32_t* in, int64_t ld_in, float* out, int64_t ld_out, int rows, int cols, int R,
+                            const float* g, int64_t planes, hipStream_t stream) {
+  const int Re = R < cols - 1 ? R : cols - 1;
+  const size_t row = sizeof(float) * blur_row_floats(cols, Re), taps = sizeof(float) * (2 * Re + 1);
+  // rows per workgroup: a window of kOut outputs per thread where the row is
+  // short, within 64 KB so that two workgroups share a CU
+  const int groups = (cols + kOut - 1) / kOut;
+  int per = groups < 256 ? 256 / groups : 1;
+  while (per > 1 && per * row + taps > 64 * 1024) --per;
+  if (per > rows) per = rows;
+  const size_t lds = per * row + taps;
+  const hipError_t e = allow_lds(&k_blur_rows<uint32_t>, lds);
+  if (e != hipSuccess) return e;
+  hipLaunchKernelGGL(k_blur_rows<uint32_t>, dim3(static_cast<uint32_t>((rows + per - 1) / per), static_cast<uint32_t>(planes)),
+                     dim3(256), lds, stream, in, ld_in, out, ld_out, rows, cols, Re, per, g);
+  return hipGetLastError();
+}
+
+// 32-column strips where two of them fit a CU's LDS, else 16 where one does
+// (half as many bytes per global read), else the tap-by-tap form.
+template <typename WT, int MODE>
+hipError_t launch_blur_cols(const float* t, int64_t ld_t, int rows, int cols, int R, const float* g, float* den_out,
+                            const float* den, WT* W, int64_t ldw, int64_t planes, hipStream_t stream) {
+  const int Re = R < rows - 1 ? R : rows - 1;
+  const size_t taps = sizeof(float) * (2 * Re + 1);
+  const size_t cells = static_cast<size_t>(rows) + 2 * Re + 2 * kOut;
+  const size_t wide = taps + sizeof(float) * cells * blur_col_stride<32>();
+  const size_t narrow = taps + sizeof(float) * cells * blur_col_stride<16>();
+  const uint32_t np = static_cast<uint32_t>(planes);
+  if (wide <= kLdsBytes / 2 || (wide <= kLdsBytes && narrow > kLdsBytes / 2)) {
+    const hipError_t e = allow_lds(&k_blur_cols<WT, MODE, 32>, wide);
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL((k_blur_cols<WT, MODE, 32>), dim3(static_cast<uint32_t>((cols + 31) / 32), np), dim3(kColThreads), wide,
+                       stream, t, ld_t, rows, cols, Re, g, den_out, den, W, ldw);
+  } else if (narrow <= kLdsBytes) {
+    const hipError_t e = allow_lds(&k_blur_cols<WT, MODE, 16>, narrow);
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL((k_blur_cols<WT, MODE, 16>), dim3(static_cast<uint32_t>((cols + 15) / 16), np), dim3(kColThreads),
+                       narrow, stream, t, ld_t, rows, cols, Re, g, den_out, den, W, ldw);
+  } else {
+    const size_t tall = sizeof(float) * static_cast<size_t>(rows) * kStrip;
+    const hipError_t e = allow_lds(&k_blur_cols_tall<WT, MODE>, tall);
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL((k_blur_cols_tall<WT, MODE>), dim3(static_cast<uint32_t>((cols + kStrip - 1) / kStrip), np),
+                       dim3(256), tall, stream, t, ld_t, rows, cols, R, g, den_out, den, W, ldw);
+  }
+  return hipGetLastError();
 }
 
 // Streaming blur + write-back (R <= kStreamMaxR, one instantiation per
@@ -252,24 +430,11 @@ hipError_t launch_update_finish(void* W, int weights, int64_t F, int64_t ldw, in
                                 hipStream_t stream) {
   const int64_t N = static_cast<int64_t>(rows) * cols;
   hipLaunchKernelGGL(k_taps, dim3(static_cast<uint32_t>(R / 256 + 1)), dim3(256), 0, stream, sigma, R, taps);
-  const size_t row_lds = sizeof(float) * static_cast<size_t>(cols);
-  const size_t col_lds = sizeof(float) * static_cast<size_t>(rows) * kStrip;
-  const uint32_t strips = static_cast<uint32_t>((cols + kStrip - 1) / kStrip);
-  {
-    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_blur_rows<uint32_t>),
-                                       hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(row_lds));
-    if (e != hipSuccess) return e;
-  }
-  for (auto f : {reinterpret_cast<const void*>(&k_blur_cols<float, 0>), reinterpret_cast<const void*>(&k_blur_cols<float, 1>),
-                 reinterpret_cast<const void*>(&k_blur_cols<_Float16, 1>)}) {
-    hipError_t e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(col_lds));
-    if (e != hipSuccess) return e;
-  }
   // denominators: the blurred counts
-  hipLaunchKernelGGL(k_blur_rows<uint32_t>, dim3(static_cast<uint32_t>(rows), 1), dim3(256), row_lds, stream, count,
-                     N, den_tmp, N, cols, R, taps);
-  hipLaunchKernelGGL((k_blur_cols<float, 0>), dim3(strips, 1), dim3(256), col_lds, stream, den_tmp, N, rows, cols, R,
-                     taps, den, nullptr, nullptr, int64_t(0));
+  hipError_t e = launch_blur_rows(count, N, den_tmp, N, rows, cols, R, taps, 1, stream);
+  if (e != hipSuccess) return e;
+  e = launch_blur_cols<float, 0>(den_tmp, N, rows, cols, R, taps, den, nullptr, nullptr, 0, 1, stream);
+  if (e != hipSuccess) return e;
   if (R <= kStreamMaxR) {
     // numerators streamed down 64-column strips, written back through den
     if (weights == kWeightsF16)
@@ -280,17 +445,14 @@ hipError_t launch_update_finish(void* W, int weights, int64_t F, int64_t ldw, in
   // chunk buffer, then the column pass written back through den
   for (int64_t f0 = 0; f0 < F; f0 += chunk_planes) {
     const int64_t fc = F - f0 < chunk_planes ? F - f0 : chunk_planes;
-    hipLaunchKernelGGL(k_blur_rows<uint32_t>, dim3(static_cast<uint32_t>(rows), static_cast<uint32_t>(fc)), dim3(256),
-                       row_lds, stream, acc + f0 * ld_acc, ld_acc, chunk, N, cols, R, taps);
+    e = launch_blur_rows(acc + f0 * ld_acc, ld_acc, chunk, N, rows, cols, R, taps, fc, stream);
+    if (e != hipSuccess) return e;
     if (weights == kWeightsF16)
-      hipLaunchKernelGGL((k_blur_cols<_Float16, 1>), dim3(strips, static_cast<uint32_t>(fc)), dim3(256), col_lds,
-                         stream, chunk, N, rows, cols, R, taps, nullptr, den,
-                         static_cast<_Float16*>(W) + f0 * ldw, ldw);
+      e = launch_blur_cols<_Float16, 1>(chunk, N, rows, cols, R, taps, nullptr, den,
+                                        static_cast<_Float16*>(W) + f0 * ldw, ldw, fc, stream);
     else
-      hipLaunchKernelGGL((k_blur_cols<float, 1>), dim3(strips, static_cast<uint32_t>(fc)), dim3(256), col_lds,
-                         stream, chunk, N, rows, cols, R, taps, nullptr, den, static_cast<float*>(W) + f0 * ldw,
-                         ldw);
-    hipError_t e = hipGetLastError();
+      e = launch_blur_cols<float, 1>(chunk, N, rows, cols, R, taps, nullptr, den, static_cast<float*>(W) + f0 * ldw,
+                                     ldw, fc, stream);
     if (e != hipSuccess) return e;
   }
   return hipGetLastError();
