@@ -133,7 +133,8 @@ typedef struct som_bmu_opts {
                             (kernel 3: super-tile) starts its union at an entry (a stage) given
                             by its place in its XCD's share of the launch and wraps round, so
                             that the tiles an XCD runs at once sweep the same feature range
-                            together and share its L2 (on the topic workload measured 19%
+                            together and share its L2 (on the list form, first the rows that
+                            many of a tile's documents hold; on the topic workload measured 19%
                             faster with kernel 3 and 17% with fp16 kernel 1; within 1.3% on
                             the Zipf maps).  A document's dot product is then summed in that
                             order, which depends on the plan, the launch's tile grid and the

@@ -356,7 +356,7 @@ hipError_t build_plan(const int32_t* indptr, const int32_t* indices, int64_t B, 
                       const int32_t* perm, const Plan& p, void* plan, const PlanLayout& l,
                       hipStream_t stream) {
   if (p.list_docs)
-    return som::launch_list_plan(indptr, indices, B, F, perm, p.list_docs, at<int32_t>(plan, l.offset),
+    return som::launch_list_plan(indptr, indices, B, F, perm, p.list_docs, p.rotate, at<int32_t>(plan, l.offset),
                                  at<int32_t>(plan, l.count), at<unsigned char>(plan, l.feat),
                                  at<uint32_t>(plan, l.start), stream);
   if (p.kernel == 1 || p.kernel == 3)

@@ -63,11 +63,16 @@ hipError_t launch_tile_plan(const int32_t* indptr, const int32_t* indices, int64
 // cut into stages of kListRows, and per (stage, wave) a list of 16-bit entries,
 // one per membership: the document's place in the wave in the low bits, the
 // row's slot offset (a multiple of kListRowBytes) above; padded to whole units
-// of four.  Space is counted in stage capacities: ceil(nnz / kListRows) per tile
+// of four.  Rows that at least 3/8 of a 256-document tile's documents hold (its
+// dense rows, where there are kListDenseMin of them or more, at most kListRows;
+// rotated sweeps only, since they break the ascending order) come before the
+// others and have no entries: each document has a 64-bit mask of those it holds.
+// Space is counted in stage capacities: ceil(nnz / kListRows) per tile
 // bound its stages (a union row has a nonzero); tile_offset is their exclusive
-// scan, tile_count the stages in use.  A tile's bytes in `data` start at
-// tile_offset * kListCapBytes: the ids of its stages (int32, padded with 0),
-// then its lists.  Its words of `start` begin at tile_offset * kListWaves + t:
+// scan, tile_count the stages in use, and in its upper half the dense rows.  A
+// tile's bytes in `data` start at tile_offset * kListCapBytes: with dense rows
+// its documents' masks (eight bytes each, no more than the dense rows' entries
+// would take), the ids of its stages (int32, padded with 0), then its lists.  Its words of `start` begin at tile_offset * kListWaves + t:
 // the start of list i = stage * kListWaves + wave, in units from the tile's
 // first list; list i + 1 follows.
 constexpr int kListWaves = 8;
@@ -77,9 +82,15 @@ constexpr int kListCapBytes = kListRows * (4 + 2) + kListWaves * 3 * 2;
 constexpr int kListStageWork = 128;  // a stage's fixed cost in entries, for the phase of rotated sweeps
 constexpr int kListPhaseWgs = 96;    // phase period in workgroups per XCD
 constexpr int64_t kListMaxF = 65536;  // the plan kernel's tables fit the LDS
+constexpr int kListDenseShare = 3;            // a dense row's holders: eighths of the documents
+constexpr int kListDenseMin = 16;
+constexpr int64_t kListDenseMaxF = 32768;     // the plan kernel's counts fit the LDS
+// masks: kListWaves * DW * 8 bytes; entries saved: kListDenseMin rows of
+// kListWaves * DW * kListDenseShare / 8 entries of 2 bytes
+static_assert(kListDenseMin * 2 * kListDenseShare >= 8 * 8, "the masks fit the space of the entries they replace");
 static_assert(kListCapBytes % 16 == 0, "a tile's ids are read 16 bytes at a time");
 hipError_t launch_list_plan(const int32_t* indptr, const int32_t* indices, int64_t B, int64_t F,
-                            const int32_t* perm, int DW, int32_t* tile_offset, int32_t* tile_count,
+                            const int32_t* perm, int DW, bool dense, int32_t* tile_offset, int32_t* tile_count,
                             unsigned char* data, uint32_t* start, hipStream_t stream);
 
 // Document-group plan (for the documents-on-lanes search): per group of D

@@ -3,16 +3,17 @@
 // (stage of kListRows union rows, wave) the list of its documents' memberships
 // that search_list.h walks.
 //
-// One workgroup of kListWaves waves per tile.  The union is a bitmap over the
-// features in LDS; with a prefix count per word, a feature's union row is one
-// LDS read and a bit count.  Wave w reads its DW documents' features three
-// times (they stay in the L2): to mark the bitmap, to count its memberships per
-// stage, and to place them; a document's features ascend, so those of one stage
-// are a run of neighbouring lanes whose first lane owns the counter.  Only wave
-// w touches list (stage, w), in document order, so the plan is the same on
-// every run.  Bound: the latency of the document reads (perm, indptr, then
-// indices), which four documents in flight per wave and several workgroups per
-// CU hide.
+// One workgroup of kListWaves waves per tile.  The features' counts in LDS
+// (DENSE) give the dense rows and the rest of the union as bitmaps; with a prefix
+// count per word, a feature's union row is one LDS read and a bit count.  Wave w
+// reads its DW documents' features three times (they stay in the L2): to mark or
+// count them, to count its lists' lengths (and set its documents' dense-row
+// masks), and to place the entries; a document's features ascend, so those of
+// one stage are a run of neighbouring lanes whose first lane owns the counter.
+// Only wave w touches list (stage, w), in document order, so the plan is the
+// same on every run.  Bound: the latency of the document reads (perm, indptr,
+// then indices), which four documents in flight per wave and several workgroups
+// per CU hide.
 #include "common.h"
 
 namespace som {
@@ -20,6 +21,10 @@ namespace {
 
 constexpr int kThreads = kListWaves * 64;
 constexpr int S = kListWaves, R = kListRows;
+
+// Slot row of union row k of a stage: the search loads rows 4 * half + i of each
+// wave's eight as its i-th pair.
+__device__ __forceinline__ uint32_t slot_row(uint32_t k) { return (k & ~7u) | ((k & 3u) << 1) | ((k >> 2) & 1u); }
 
 // Stage capacities of each tile.  One wave per tile.
 __global__ void __launch_bounds__(256)
@@ -123,22 +128,28 @@ __device__ __forceinline__ void for_each_feature(const int32_t* __restrict__ ind
   }
 }
 
-template <int DW>
+// DENSE: find the tile's dense rows (F at most kListDenseMaxF).
+template <int DW, bool DENSE>
 __global__ void __launch_bounds__(kThreads)
 k_list_plan(const int32_t* __restrict__ indptr, const int32_t* __restrict__ indices, const int32_t* __restrict__ perm,
             int64_t B, int32_t words, const int32_t* __restrict__ tile_offset, int32_t* __restrict__ tile_count,
             unsigned char* __restrict__ data, uint32_t* __restrict__ start) {
   extern __shared__ uint32_t lds[];
-  uint32_t* bits = lds;                       // [words] the union
-  uint32_t* before = lds + words;             // [words] union rows in earlier words
-  volatile int32_t* list = reinterpret_cast<volatile int32_t*>(lds + 2 * words);  // [stages * S] lengths, then cursors
+  uint32_t* bits = lds;                       // [words] the union's rows with entry lists
+  uint32_t* before = lds + words;             // [words] such rows in earlier words
+  uint32_t* dense = lds + 2 * words;          // [words] the dense rows
+  uint32_t* dense_before = lds + 3 * words;   // [words]
+  uint32_t* mask = lds + 4 * words;           // [S * DW][2] the documents' dense rows
+  // [stages * S] lengths of the lists, then cursors; before that (DENSE) 16-bit
+  // counts of the documents that hold each feature
+  uint32_t* counts = mask + 2 * S * DW;
+  volatile int32_t* list = reinterpret_cast<volatile int32_t*>(counts);
   __shared__ int32_t wsum[kListWaves];
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int64_t t = blockIdx.x;
   const int64_t cap0 = tile_offset[t];
   unsigned char* base = data + cap0 * kListCapBytes;
-  int32_t* ids = reinterpret_cast<int32_t*>(base);
   int32_t begin = 0, end = 0;
   {
     const int64_t p = t * (S * DW) + wave * DW + lane;
@@ -148,56 +159,108 @@ k_list_plan(const int32_t* __restrict__ indptr, const int32_t* __restrict__ indi
       end = indptr[d + 1];
     }
   }
-  for (int i = tid; i < words; i += kThreads) bits[i] = 0u;
-  __syncthreads();
-  for_each_feature<DW>(indices, begin, end, lane, [&](int32_t f, bool on, int) {
-    if (on) atomicOr(&bits[f >> 5], 1u << (f & 31));
-  });
-  __syncthreads();
-  // prefix counts over a contiguous run of words per thread, and the ids
+  // a contiguous run of words per thread
   const int per = (words + kThreads - 1) / kThreads;
   const int w0 = tid * per, w1 = w0 + per < words ? w0 + per : words;
+  int32_t nd = 0;   // dense rows
+  if (DENSE) {
+    for (int i = tid; i < 2 * S * DW; i += kThreads) mask[i] = 0u;
+    for (int i = tid; i < words * 16; i += kThreads) counts[i] = 0u;
+    __syncthreads();
+    for_each_feature<DW>(indices, begin, end, lane, [&](int32_t f, bool on, int) {
+      if (on) atomicAdd(&counts[f >> 1], 1u << ((f & 1) * 16));
+    });
+    __syncthreads();
+    int32_t c = 0;
+    for (int i = w0; i < w1; ++i) {
+      uint32_t any = 0u, many = 0u;
+      for (int k = 0; k < 16; ++k) {
+        const uint32_t v = counts[i * 16 + k];
+        const uint32_t lo = v & 0xffffu, hi = v >> 16;
+        any |= (lo ? 1u : 0u) << (2 * k) | (hi ? 1u : 0u) << (2 * k + 1);
+        many |= (lo >= S * DW * kListDenseShare / 8 ? 1u : 0u) << (2 * k) |
+                (hi >= S * DW * kListDenseShare / 8 ? 1u : 0u) << (2 * k + 1);
+      }
+      bits[i] = any;
+      dense[i] = many;
+      c += __popc(many);
+    }
+    int32_t at = block_scan(c, wsum, &nd);
+    // at most one stage of them, the first by id; too few are left to the lists
+    nd = nd < kListDenseMin ? 0 : (nd < R ? nd : R);
+    for (int i = w0; i < w1; ++i) {
+      dense_before[i] = static_cast<uint32_t>(at);
+      uint32_t keep = 0u;
+      for (uint32_t m = dense[i]; m && at < nd; m &= m - 1, ++at) keep |= m & (~m + 1u);
+      dense[i] = keep;
+      bits[i] &= ~keep;
+    }
+  } else {
+    for (int i = tid; i < words; i += kThreads) bits[i] = 0u;
+    __syncthreads();
+    for_each_feature<DW>(indices, begin, end, lane, [&](int32_t f, bool on, int) {
+      if (on) atomicOr(&bits[f >> 5], 1u << (f & 31));
+    });
+  }
+  __syncthreads();
+  // prefix counts, and the ids: the dense rows, then the others
   int32_t c = 0;
   for (int i = w0; i < w1; ++i) c += __popc(bits[i]);
   int32_t cnt;
-  int32_t u = block_scan(c, wsum, &cnt);
+  int32_t u = block_scan(c, wsum, &cnt) + nd;
+  cnt += nd;
   const int32_t nst = (cnt + R - 1) / R;
+  int32_t* ids = reinterpret_cast<int32_t*>(base + (nd ? S * DW * 8 : 0));
   for (int i = w0; i < w1; ++i) {
     before[i] = static_cast<uint32_t>(u);
     for (uint32_t m = bits[i]; m; m &= m - 1) ids[u++] = i * 32 + __builtin_ctz(m);
+    if (DENSE) {
+      int32_t k = static_cast<int32_t>(dense_before[i]);
+      for (uint32_t m = dense[i]; m; m &= m - 1) ids[k++] = i * 32 + __builtin_ctz(m);
+    }
   }
   for (int i = cnt + tid; i < nst * R; i += kThreads) ids[i] = 0;
-  for (int i = tid; i < nst * S; i += kThreads) list[i] = 0;
-  if (tid == 0) tile_count[t] = nst;
+  for (int i = tid; i < nst * S; i += kThreads) list[i] = 0;   // (the counts are done with)
+  if (tid == 0) tile_count[t] = nst | nd << 16;
   __syncthreads();
 
-  // runs of one stage within a call: the first lane of each (leader), its
-  // length, and each lane's place in its run
+  // A call's lanes by stage: the first lane of each run (leader), the entries
+  // of the run, and each lane's place among them.  A dense row's lane counts
+  // with the row that would stand in its place.
   struct Run {
-    int32_t row, list, length, place;
-    bool leader;
+    int32_t row, list, entries, place;
+    bool leader, entry;
   };
   auto run_of = [&](int32_t f, bool on) {
     Run r;
-    const uint32_t w = bits[f >> 5];
-    r.row = static_cast<int32_t>(before[f >> 5]) + __popc(w & ((1u << (f & 31)) - 1u));
-    const int32_t stage = on ? r.row / R : -1;
+    const uint32_t m = 1u << (f & 31), w = bits[f >> 5];
+    r.row = static_cast<int32_t>(before[f >> 5]) + __popc(w & (m - 1u));
+    r.entry = on && (w & m) != 0u;
+    const int32_t stage = on ? (r.row / R < nst ? r.row / R : nst - 1) : -1;
     r.list = stage * S + wave;
     const int32_t prev = __shfl_up(stage, 1, 64);
     r.leader = on && (lane == 0 || prev != stage);
-    const uint64_t leaders = __ballot(r.leader);
-    const int active = __popcll(__ballot(on));         // the lanes with a feature come first
-    const uint64_t upto = (((1ull << lane) - 1ull) << 1) | 1ull;
+    const uint64_t leaders = __ballot(r.leader), with = __ballot(r.entry);
+    const uint64_t below = (1ull << lane) - 1ull, upto = (below << 1) | 1ull;
     const uint64_t later = leaders & ~upto;
-    r.length = (later ? __builtin_ctzll(later) : active) - lane;
-    r.place = lane - (63 - __builtin_clzll((leaders & upto) | 1ull));
+    const uint64_t until = later ? (later & (~later + 1ull)) - 1ull : ~0ull;    // lanes before the next leader
+    const int first = 63 - __builtin_clzll((leaders & upto) | 1ull);
+    const uint64_t run = with & until & ~((1ull << first) - 1ull);
+    r.entries = __popcll(run);
+    r.place = __popcll(run & below);
     return r;
   };
-  for_each_feature<DW>(indices, begin, end, lane, [&](int32_t f, bool on, int) {
+  for_each_feature<DW>(indices, begin, end, lane, [&](int32_t f, bool on, int s) {
     const Run r = run_of(f, on);
-    if (r.leader) list[r.list] += r.length;
+    if (r.leader) list[r.list] += r.entries;
+    if (DENSE && on && !r.entry) {
+      const uint32_t d = slot_row(dense_before[f >> 5] + __popc(dense[f >> 5] & ((1u << (f & 31)) - 1u)));
+      atomicOr(&mask[2 * (wave * DW + s) + (d >> 5)], 1u << (d & 31));
+    }
   });
   __syncthreads();
+  if (nd)
+    for (int i = tid; i < 2 * S * DW; i += kThreads) reinterpret_cast<uint32_t*>(base)[i] = mask[i];
   // starts of the lists in units of four entries; lengths become cursors
   uint32_t* st = start + cap0 * S + t;
   int32_t units = 0;
@@ -214,18 +277,14 @@ k_list_plan(const int32_t* __restrict__ indptr, const int32_t* __restrict__ indi
   }
   if (tid == 0) st[nst * S] = static_cast<uint32_t>(units);
   __syncthreads();
-  uint16_t* entries = reinterpret_cast<uint16_t*>(base + nst * (R * 4));
+  uint16_t* entries = reinterpret_cast<uint16_t*>(ids + nst * R);
   for_each_feature<DW>(indices, begin, end, lane, [&](int32_t f, bool on, int s) {
     const Run r = run_of(f, on);
-    if (on) {
-      // slot row of union row k of the stage: the search loads rows 4 * half +
-      // i of each wave's eight as its i-th pair
-      const int32_t k = r.row % R;
-      const int32_t slot_row = (k & ~7) | ((k & 3) << 1) | ((k >> 2) & 1);
-      entries[list[r.list] + r.place] = static_cast<uint16_t>(slot_row * kListRowBytes + s);
+    if (r.entry) {
+      entries[list[r.list] + r.place] = static_cast<uint16_t>(slot_row(r.row % R) * kListRowBytes + s);
     }
     __builtin_amdgcn_wave_barrier();
-    if (r.leader) list[r.list] += r.length;   // after every lane's read: LDS operations of a wave keep their order
+    if (r.leader) list[r.list] += r.entries;   // after every lane's read: LDS operations of a wave keep their order
     __builtin_amdgcn_wave_barrier();
   });
   __syncthreads();
@@ -236,7 +295,7 @@ k_list_plan(const int32_t* __restrict__ indptr, const int32_t* __restrict__ indi
 }  // namespace
 
 hipError_t launch_list_plan(const int32_t* indptr, const int32_t* indices, int64_t B, int64_t F,
-                            const int32_t* perm, int DW, int32_t* tile_offset, int32_t* tile_count,
+                            const int32_t* perm, int DW, bool dense, int32_t* tile_offset, int32_t* tile_count,
                             unsigned char* data, uint32_t* start, hipStream_t stream) {
   if (F > kListMaxF || (DW != 16 && DW != 32)) return hipErrorInvalidValue;
   const int D = S * DW;
@@ -244,18 +303,16 @@ hipError_t launch_list_plan(const int32_t* indptr, const int32_t* indices, int64
   hipLaunchKernelGGL(k_list_nnz, dim3(static_cast<uint32_t>((ntiles + 3) / 4)), dim3(256), 0, stream, indptr, perm, B,
                      D, ntiles, tile_count);
   hipLaunchKernelGGL(k_list_scan, dim3(1), dim3(1024), 0, stream, tile_count, ntiles, tile_offset);
+  dense = dense && DW == 32 && F <= kListDenseMaxF;
   const int32_t words = static_cast<int32_t>((F + 31) / 32);
-  const int64_t stages = (F + R - 1) / R;
-  const size_t bytes = sizeof(uint32_t) * (2 * static_cast<size_t>(words) + static_cast<size_t>(stages) * S);
-  const void* fn = DW == 16 ? reinterpret_cast<const void*>(k_list_plan<16>) : reinterpret_cast<const void*>(k_list_plan<32>);
-  hipError_t e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(bytes));
+  const size_t lists = static_cast<size_t>((F + R - 1) / R) * S, counts = dense ? static_cast<size_t>(words) * 16 : 0;
+  const size_t bytes = sizeof(uint32_t) * (4 * static_cast<size_t>(words) + 2 * D + (lists > counts ? lists : counts));
+  auto* kernel = DW == 16 ? &k_list_plan<16, false> : dense ? &k_list_plan<32, true> : &k_list_plan<32, false>;
+  const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kernel),
+                                           hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(bytes));
   if (e != hipSuccess) return e;
-  if (DW == 16)
-    hipLaunchKernelGGL(k_list_plan<16>, dim3(static_cast<uint32_t>(ntiles)), dim3(kThreads), bytes, stream, indptr,
-                       indices, perm, B, words, tile_offset, tile_count, data, start);
-  else
-    hipLaunchKernelGGL(k_list_plan<32>, dim3(static_cast<uint32_t>(ntiles)), dim3(kThreads), bytes, stream, indptr,
-                       indices, perm, B, words, tile_offset, tile_count, data, start);
+  hipLaunchKernelGGL(kernel, dim3(static_cast<uint32_t>(ntiles)), dim3(kThreads), bytes, stream, indptr, indices, perm,
+                     B, words, tile_offset, tile_count, data, start);
   return hipGetLastError();
 }
 

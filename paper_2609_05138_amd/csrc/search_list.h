@@ -17,14 +17,15 @@
 // unit's reads are issued before the previous unit's adds.
 //
 // What bounds it: vector issue and the LDS reads, three vector instructions and
-// 512 bytes per entry (on the 512^2 map a 262,144-document batch spends about
-// 260 of its 525 ms in the lists, the rest in stage barriers and the stages'
-// fixed instructions; the row loads alone take 300 ms and overlap).  Kernel 3
+// 512 bytes per entry (on the 512^2 map a 262,144-document batch took 523 ms with
+// every row in the lists, about 260 of them in the lists, the rest in stage
+// barriers and the stages' fixed instructions; the row loads alone took 300 ms
+// and overlap; 504 with the rows that many documents hold on the matrix cores).  Kernel 3
 // took 545 ms there: its 64-document tiles of 256-neuron slices need 484 ms of
 // row loads (33.6 rows per document at a working set of 20 MB per slice against
 // 21.7 rows at 10 MB) and a scalar test per document and 16-row stage.  On the
-// 512^2 topic batch, which the row loads bound, 131,072 documents took 449 ms
-// (kernel 3: 648); the 128^2 map's 65,536-document search 8.4 ms (11.0).
+// 512^2 topic batch, which the row loads bound, 131,072 documents took 449-455 ms
+// (kernel 3: 648); the 128^2 map's 65,536-document pass 8.4 ms (12.0).
 // Measured and not kept: rows held by one document loaded straight into
 // registers by the document's wave (575 ms: the loads wait for each other, where
 // the staged ones are in flight together), and scalar copies of the next list's
@@ -150,12 +151,61 @@ struct ListAcc<16, NPL> {
                    : SOM_L_OPERANDS("+{s[32:39]}", "=&{s[40:47]}") : SOM_L_INPUTS : SOM_L_CLOBBERS, SOM_L_SPARE);   \
     return nset;                                                                                                    \
   }
+// The dense rows.  A row's products with a wave's 32 documents, into the plane of
+// accumulators from register BASE on; v W: its weights, v H: 1 where lane s's
+// document holds it, else 0.
+#define SOM_L_MFMA(BASE, I, W, H)                                                                                  \
+  "v_mfma_f32_4x4x1_16b_f32 v[" #BASE "+4*" #I ":" #BASE "+4*" #I "+3], v" #H ", v" #W ", v[" #BASE "+4*" #I       \
+  ":" #BASE "+4*" #I "+3] cbsz:4 abid:" #I "\n\t"
+#define SOM_L_MFMA32(BASE, W, H)                                                                               \
+  SOM_L_MFMA(BASE, 0, W, H) SOM_L_MFMA(BASE, 1, W, H) SOM_L_MFMA(BASE, 2, W, H) SOM_L_MFMA(BASE, 3, W, H)      \
+  SOM_L_MFMA(BASE, 4, W, H) SOM_L_MFMA(BASE, 5, W, H) SOM_L_MFMA(BASE, 6, W, H) SOM_L_MFMA(BASE, 7, W, H)
+#define SOM_L_HELD(K, H) "v_bfe_u32 v" #H ", %[lo], " #K ", 1\n\tv_cvt_f32_u32_e32 v" #H ", v" #H "\n\t"
+// Four rows per step, two vector instructions and a wait state before the first
+// product; after the last, the wait states until other instructions may read
+// the sums.  special: row by row, each holder by the lists' indexed add.
+#define SOM_L_DENSE                                                                                               \
+  "s_cmp_lg_u32 %[special], 0\n\ts_cbranch_scc1 .Lsom_special%=\n"                                                \
+  ".Lsom_four%=:\n\t"                                                                                             \
+  "ds_read_b64 v[24:25], %[row]\n\tds_read_b64 v[26:27], %[row] offset:512\n\t"                                   \
+  "ds_read_b64 v[28:29], %[row] offset:1024\n\tds_read_b64 v[30:31], %[row] offset:1536\n\t"                      \
+  SOM_L_HELD(0, 32) SOM_L_HELD(1, 33) SOM_L_HELD(2, 34) SOM_L_HELD(3, 35)                                         \
+  "v_alignbit_b32 %[lo], %[hi], %[lo], 4\n\tv_lshrrev_b32_e32 %[hi], 4, %[hi]\n\tv_add_u32_e32 %[row], 0x800, %[row]\n\t"                                  \
+  "s_waitcnt lgkmcnt(0)\n\ts_nop 1\n\t"                                                                           \
+  SOM_L_PRODUCTS(24, 25, 32) SOM_L_PRODUCTS(26, 27, 33) SOM_L_PRODUCTS(28, 29, 34) SOM_L_PRODUCTS(30, 31, 35)     \
+  "s_sub_u32 %[n], %[n], 4\n\ts_cmp_lg_u32 %[n], 0\n\ts_cbranch_scc1 .Lsom_four%=\n\t"                            \
+  "s_nop 7\n\ts_nop 7\n\ts_branch .Lsom_done%=\n"                                                                 \
+  ".Lsom_special%=:\n\t"                                                                                          \
+  "ds_read_b64 v[24:25], %[row]\n\t"                                                                              \
+  "v_and_b32_e32 v32, 1, %[lo]\n\tv_cmp_ne_u32_e32 vcc, 0, v32\n\ts_nop 4\n\t"                                 \
+  "s_mov_b32 s48, vcc_lo\n\ts_waitcnt lgkmcnt(0)\n"                                                                 \
+  ".Lsom_holder%=:\n\t"                                                                                           \
+  "s_cmp_eq_u32 s48, 0\n\ts_cbranch_scc1 .Lsom_next%=\n\t"                                                        \
+  "s_ff1_i32_b32 s49, s48\n\ts_bitset0_b32 s48, s49\n\t"                                                          \
+  "s_set_gpr_idx_on s49, " SOM_L_MODE "\n\t" SOM_L_ADD(24, 25) "s_set_gpr_idx_off\n\t"                            \
+  "s_branch .Lsom_holder%=\n"                                                                                     \
+  ".Lsom_next%=:\n\t"                                                                                             \
+  "v_alignbit_b32 %[lo], %[hi], %[lo], 1\n\tv_lshrrev_b32_e32 %[hi], 1, %[hi]\n\tv_add_u32_e32 %[row], 0x200, %[row]\n\t"                                  \
+  "s_sub_u32 %[n], %[n], 1\n\ts_cmp_lg_u32 %[n], 0\n\ts_cbranch_scc1 .Lsom_special%=\n"                           \
+  ".Lsom_done%=:\n\t"
+#define SOM_L_DEFINE_DENSE(NPL)                                                                                     \
+  __device__ __forceinline__ void add_dense_rows(ListAcc<32, NPL>& acc, uint32_t row, uint32_t n, uint32_t lo,       \
+                                                 uint32_t hi, uint32_t special) {                                   \
+    uint32_t m0;                                                                                                    \
+    asm volatile(SOM_L_DENSE                                                                                        \
+                 : "={m0}"(m0), [row] "+v"(row), [n] "+s"(n), [lo] "+v"(lo), [hi] "+v"(hi), SOM_L_ACC               \
+                 : [special] "s"(special) : SOM_L_CLOBBERS, "vcc", SOM_L_SPARE);                                    \
+  }
 // fp32 rows: two neurons per lane
 #define SOM_L_MODE "gpr_idx(SRC0,DST)"
 #define SOM_L_ADD(R, R1) "v_add_f32_e32 v40, v40, v" #R "\n\tv_add_f32_e32 v74, v74, v" #R1 "\n\t"
 #define SOM_L_ACC "+{v[40:71]}"(acc.p[0]), "+{v[74:105]}"(acc.p[1])
 #define SOM_L_SPARE "v72", "v106"
+#define SOM_L_PRODUCTS(R, R1, H) \
+  SOM_L_MFMA32(40, R, H) SOM_L_MFMA32(74, R1, H)
 SOM_L_DEFINE(32, 2)
+SOM_L_DEFINE_DENSE(2)
+#undef SOM_L_PRODUCTS
 #undef SOM_L_ADD
 #undef SOM_L_ACC
 #undef SOM_L_SPARE
@@ -167,6 +217,9 @@ SOM_L_DEFINE(16, 2)
 #undef SOM_L_ACC
 #undef SOM_L_SPARE
 #undef SOM_L_MODE
+#define SOM_L_WIDEN(R, R1) \
+  "v_cvt_f32_f16_e32 v36, v" #R "\n\tv_cvt_f32_f16_sdwa v37, v" #R " dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:WORD_1\n\t" \
+  "v_cvt_f32_f16_e32 v38, v" #R1 "\n\tv_cvt_f32_f16_sdwa v39, v" #R1 " dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:WORD_1\n\ts_nop 1\n\t"
 // fp16 rows: four neurons per lane, each half widened and added by one fused
 // multiply-add with 1.0 (exact product, one rounding: the widened add)
 #define SOM_L_MODE "gpr_idx(SRC2,DST)"
@@ -182,11 +235,65 @@ SOM_L_DEFINE(16, 4)
 #define SOM_L_ADD(R, R1) SOM_L_MIX(40, R, 0) SOM_L_MIX(74, R, 1) SOM_L_MIX(108, R1, 0) SOM_L_MIX(142, R1, 1)
 #define SOM_L_ACC "+{v[40:71]}"(acc.p[0]), "+{v[74:105]}"(acc.p[1]), "+{v[108:139]}"(acc.p[2]), "+{v[142:173]}"(acc.p[3])
 #define SOM_L_SPARE "v72", "v106", "v140", "v174"
+#define SOM_L_PRODUCTS(R, R1, H) \
+  SOM_L_WIDEN(R, R1) SOM_L_MFMA32(40, 36, H) SOM_L_MFMA32(74, 37, H) SOM_L_MFMA32(108, 38, H) SOM_L_MFMA32(142, 39, H)
 SOM_L_DEFINE(32, 4)
+SOM_L_DEFINE_DENSE(4)
+#undef SOM_L_PRODUCTS
 #undef SOM_L_ADD
 #undef SOM_L_ACC
 #undef SOM_L_SPARE
 #undef SOM_L_MODE
+
+typedef uint32_t u32x2w __attribute__((ext_vector_type(2)));
+
+// A lane's 8 bytes of a row as its neurons' weights.
+template <typename WT, int NPL>
+__device__ __forceinline__ void widen(u32x2w raw, float (&w)[NPL]) {
+  if constexpr (sizeof(WT) == 4) {
+    w[0] = __uint_as_float(raw.x);
+    w[1] = __uint_as_float(raw.y);
+  } else {
+    typedef _Float16 half4 __attribute__((ext_vector_type(4)));
+    const half4 v = __builtin_bit_cast(half4, raw);
+#pragma unroll
+    for (int q = 0; q < NPL; ++q) w[q] = static_cast<float>(v[q]);
+  }
+}
+
+// Adds the dense rows (nd of them, in the first rows of the slot; ring + row: the
+// lane's 8 bytes of slot row 0) on the matrix cores: v_mfma_f32_4x4x1 multiplies
+// four documents' 0 or 1 (one block of A, named by the instruction and broadcast
+// to all sixteen) with the lane's neuron of one row, and adds into the four
+// documents' accumulators, which lie as the lists' adds have them (lane =
+// neuron, register = document).  8 * NPL of them add a row into the wave's 32
+// documents; the products are exact and each sum is rounded once, as an add is.
+// The 16 instructions of a row of fp32 weights take 128 cycles whatever it holds;
+// the lists' three per holder take about twelve, so the plan takes a row from
+// 3/8 of the documents on.  Measured, before -> after (fp32): 512^2 and 256^2 maps with 256k documents, and 1M documents on 32 x 32 -3.6%, -3.7%, -4.7% (523.2 -> 504.5, 133.5 ->
+// 128.5, 10.5 -> 10.0 ms); with 1/4 of the documents 510, 1/2 507, 3/4 536.  fp16
+// tiles (16 documents a wave) gained nothing (354 -> 355) and have lists only.
+template <typename WT, int NPL>
+__device__ __forceinline__ void add_dense(ListAcc<32, NPL>& acc, const unsigned char* ring, uint32_t row, int nd,
+                                          const unsigned char* masks, int lane) {
+  // lane s < 32: the dense rows that document s of the wave holds, by slot row
+  // (read here: kept in flight over the wait above, it delayed the stage by 2%)
+  const uint64_t held = reinterpret_cast<const uint64_t*>(masks)[lane & 31];
+  bool special = false;
+  const int n = (nd + 7) & ~7;   // (rows past the last have no holder)
+#pragma clang loop unroll(disable)
+  for (int u = 0; u < n; u += 8)
+#pragma unroll
+    for (int k = 0; k < 8; ++k) {
+      float w[NPL];
+      widen<WT, NPL>(*reinterpret_cast<const u32x2w*>(ring + row + (u + k) * kListRowBytes), w);
+#pragma unroll
+      for (int q = 0; q < NPL; ++q) special |= __builtin_amdgcn_classf(w[q], 0x207);   // an infinity or a NaN
+    }
+  // 0 times such a value is no 0: these rows are added to their holders only
+  add_dense_rows(acc, lds_offset(ring) + row, n, static_cast<uint32_t>(held), static_cast<uint32_t>(held >> 32),
+                 __builtin_amdgcn_readfirstlane(__ballot(special) != 0));
+}
 
 // Minimum of x over the wave, uniform (data-parallel-primitive row shifts, then
 // the two row broadcasts: lane 63 ends with the whole wave's).
@@ -332,11 +439,13 @@ k_search_list(SearchArgs a) {
   typedef const __attribute__((address_space(4))) int32_t* const_i32;
   typedef const __attribute__((address_space(4))) char* const_char;
   const int64_t cap0 = ((const_i32)a.tile_offset)[t];
-  const int32_t nst = ((const_i32)a.tile_count)[t];   // stages
+  const int32_t nst = ((const_i32)a.tile_count)[t] & 0xffff;   // stages
+  const int32_t nd = ((const_i32)a.tile_count)[t] >> 16;       // dense rows
   // unit offsets of the tile's lists, stage by stage: list (q, w) holds units
   // pt[q * S + w] .. pt[q * S + w + 1]
   const const_u32 pt = (const_u32)(a.list_start + cap0 * S + t);
-  const unsigned char* data = a.list_data + cap0 * kListCapBytes;
+  const unsigned char* masks = a.list_data + cap0 * kListCapBytes;
+  const unsigned char* data = masks + (nd ? S * DW * 8 : 0);
   const const_char lists = (const_char)(data + nst * (R * 4));
 
   if (nst > 0) {
@@ -398,6 +507,7 @@ k_search_list(SearchArgs a) {
     const uint32_t vl0 = ring0 | static_cast<uint32_t>(lane * 8);
     const uint32_t vm = 0xfe00u;
     const uint64_t lb = reinterpret_cast<uint64_t>((const char*)lists);
+    uint32_t sbc = static_cast<uint32_t>(q) * kStarts;   // the current stage
     // `more`: a stage follows (its loads are issued); `none`: no stage at all,
     // the filler of an odd count
     auto step = [&](auto odd, bool more, bool none) {
@@ -413,6 +523,10 @@ k_search_list(SearchArgs a) {
       sb = after(sb);
       id = load_ids(sb);
       const u32x2v next2 = load_range(sb);
+      if constexpr (DW == 32)
+        if (nd && sbc == 0 && !none)
+          add_dense<WT, NPL>(acc, ring, slot + lane * 8, nd, masks + wave * DW * 8, lane);
+      sbc = after(sbc);
       const uint32_t n = none ? ~0u : cur.y - cur.x - 1u;
       set = add_list<ODD>(acc, set, lb, cur.x * 8u, next.x * 8u, n, vl0 | slot, vm);
       cur = next;

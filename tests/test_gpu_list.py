@@ -118,3 +118,30 @@ def test_list_form_rows_of_4_gib():
     want = som.som_bmu_search_top2(W, norms, ip, ix, N=N, kernel=1, sweep=1)
     assert _equal(som.som_bmu_search_top2(W, norms, ip, ix, N=N), want)
     assert _equal(som.som_bmu_search(W, norms, ip, ix, N=N), want[:2])
+
+
+@pytest.mark.parametrize("dtype", [np.float32, np.float16])
+@pytest.mark.parametrize("dense,share,F", [(15, 0.5, 400), (16, 0.4, 400), (17, 1.0, 32768), (64, 0.3, 65), (63, 0.3, 300),
+                                           (100, 0.5, 3000), (40, 0.25, 500), (64, 1.0, 64), (40, 0.5, 32769)])
+def test_rows_that_many_documents_hold(dtype, dense, share, F):
+    # such rows of a tile (from 16 of them on, at most 64) are summed on the matrix cores
+    rng = np.random.default_rng(dense * 7 + F)
+    B, N = MIN_DOCS[dtype] + 300, 300
+    hot = np.sort(rng.choice(F, dense, replace=False))
+    rows = [np.unique(np.concatenate([hot[rng.random(dense) < share], rng.integers(0, F, rng.integers(0, 9))]))
+            for _ in range(B)]
+    rows[5] = rows[-1] = np.zeros(0, np.int64)
+    ip = torch.from_numpy(np.concatenate([[0], np.cumsum([len(r) for r in rows])]).astype(np.int32)).to(DEV)
+    ix = torch.from_numpy(np.concatenate(rows).astype(np.int32)).to(DEV)
+    W, norms = _book(rng, F, N, dtype)
+    for special in (False, True):
+        if special:   # 0 times an infinity or a NaN is no 0; finite norms, so that they show
+            # (the NaN in the last neuron of every kernel's lane: a lane takes its
+            # first neuron before it compares, whatever its distance)
+            W[hot[0], 3], W[hot[1], 7], W[hot[-1], 70], W[hot[2], 299] = np.inf, np.nan, -np.inf, np.inf
+            norms[:N:3] *= 0.5
+        want = som.som_bmu_search_top2(W, norms, ip, ix, N=N, kernel=1, sweep=1)
+        for sweep in (0, 1):
+            got = som.som_bmu_search_top2(W, norms, ip, ix, N=N, sweep=sweep)
+            assert _equal(got, want), (special, sweep)
+            assert _equal(som.som_bmu_search(W, norms, ip, ix, N=N, sweep=sweep), want[:2]), (special, sweep)
