@@ -94,7 +94,7 @@ def parse(argv=None):
     p.add_argument("--docs", type=int, default=0, help="with --batch: the first DOCS documents only")
     p.add_argument("--ldw", type=int, default=0, help="codebook row stride in floats (0 = recommended)")
     p.add_argument("--kernel", type=int, default=0,
-                   help="0 = the library's automatic choice (kernel 3 for fp32, kernel 1 for fp16), 1, 2 or 3")
+                   help="0 = the library's automatic choice (the list form, or kernel 1 for small batches), 1, 2 or 3")
     p.add_argument("--tile-docs", type=int, default=0)
     p.add_argument("--lane-neurons", type=int, default=0)
     p.add_argument("--group-tiles", type=int, default=0)
