@@ -62,18 +62,20 @@ typedef enum som_status {
  *
  * Automatic choices (measured on MI355X at map sizes 32^2 to 512^2, F =
  * 2,048 to 20,000, batches up to 1M documents): rotated union sweeps
- * (`sweep`) wherever available.  With no knob naming a kernel or a geometry,
- * batches of 1,536 documents and more (fp16: 1,024) over at most 65,536
- * features take the list form of kernel 3, whose plan holds, per tile of 256
- * documents (fp16: 128) and wave, lists of the (row, document) memberships; it
- * lives in the bytes of the kernel it stands in for; smaller batches (fp16:
- * fewer than 768 documents) take kernel 1 with two-document tiles.  Otherwise
- * (a knob given, a larger vocabulary, fp16 batches between): for an fp32
+ * (`sweep`) wherever available.  With no knob naming a kernel or a geometry:
+ * batches of up to 512 documents (fp16: 64) take kernel 1 with two-document tiles
+ * in ascending order; fp32 batches of 1,536 documents and more (fp16: 65,536) over
+ * at most 65,536 features take the list form of kernel 3, whose plan holds, per
+ * tile of 256 documents (fp16: 128) and wave, lists of the (row, document)
+ * memberships; it lives in the bytes of the kernel it stands in for.  Otherwise
+ * (a knob given, a larger vocabulary, batches between): for an fp32
  * codebook kernel 3 with 64-document super-tiles and the document-major
  * dispatch; for fp16, or when a knob only kernel 1 has is set (tile_docs of 32
  * or less, lane_neurons, group_tiles), kernel 1 with tiles of 16 documents for
  * fp32 and 8 for fp16, and four tiles per workgroup for fp32 tiles of 16
- * documents when N >= 131,072.  The automatic choices depend on the storage
+ * documents when N >= 131,072.  Below 65,536 documents the automatic launch sums
+ * in the order of these last two kernels whichever it takes, bit for bit.  The
+ * automatic choices depend on the storage
  * type: a search that plans internally uses its own (fp32 or fp16);
  * som_plan, som_plan_bytes and the planned searches use opts->storage, so a
  * plan and its search always agree on the geometry.

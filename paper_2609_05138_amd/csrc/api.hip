@@ -85,6 +85,7 @@ struct Plan {
   int chunk_slices = 1;      // kernels 1 and 3: neuron slices per schedule chunk
   bool rotate = false;       // kernel 3: rotated union sweeps (opts->sweep)
   int list_docs = 0;         // > 0: the list form, documents per wave (see choose_lists)
+  int list_form = som::kListPlain;
 };
 
 // Kernel-1 tiles per workgroup chosen automatically: four consecutive tiles
@@ -100,16 +101,13 @@ bool no_geometry(const som_bmu_opts& o) {
 }
 
 // Small batches: the automatic launch takes kernel 1 with two-document tiles,
-// one wave each, which spread a batch over the device where the shared-union
-// kernels would leave most of it idle and each of their workgroups a long chain
-// of stages; its plan is short too.  Whole search calls, F = 20,000, fp32, in
-// us (kernel 3 / this): 16 documents on 128^2 151 / 51, 256 on 32^2 260 / 50,
-// 256 on 128^2 353 / 154, 1,024 on 128^2 480 / 456 and on 256^2 1,247 / 1,222;
-// 2,048 on 128^2 737 / 788 (the list form: 532).  fp16 (kernel 1 with
-// eight-document tiles / this): 16 on 128^2 108 / 52, 256 on 128^2 124 / 96,
-// 512 on 256^2 432 / 401 and on 128^2 158 / 162, 1,024 on 128^2 234 / 284 (the
-// list form: 198).  The line depends on the batch only, as a plan does.
-constexpr int64_t kSmallDocsF32 = 1536, kSmallDocsF16 = 768;
+// one wave each, swept in ascending order, which spread a batch over the device
+// where kernel 3's super-tiles (fp16: kernel 1's eight-document tiles) would leave
+// most of it idle and each of their workgroups a long chain of stages; its plan is
+// short too.  The line is where the larger tiles' rotated sweeps start to rotate:
+// up to eight of them, one per XCD, all have phase 0, so both sum in ascending
+// order and give the same bits.
+constexpr int64_t kSmallDocsF32 = 8 * 64, kSmallDocsF16 = 8 * 8;
 constexpr int kSmallTileDocs = 2;
 
 // `weights` is the storage type of the codebook searched (it fixes the load
@@ -132,7 +130,7 @@ som_status make_plan(int64_t N, int64_t B, const som_bmu_opts* opts, Plan* p, in
   // topic workload; kernel 1 for fp16 (8-document tiles, measured faster
   // there) and whenever a knob only kernel 1 has is given
   const bool k1_knob = (o.tile_docs > 0 && o.tile_docs <= 32) || o.lane_neurons || o.group_tiles;
-  const bool small = no_geometry(o) && B < (auto16 ? kSmallDocsF16 : kSmallDocsF32);
+  const bool small = no_geometry(o) && B <= (auto16 ? kSmallDocsF16 : kSmallDocsF32);
   const int kernel = o.kernel ? o.kernel : ((auto16 || k1_knob || small) ? 1 : 3);
   p->kernel = kernel;
   if (kernel == 1) {
@@ -218,7 +216,8 @@ som_status make_plan(int64_t N, int64_t B, const som_bmu_opts* opts, Plan* p, in
     return fail(SOM_ERR_INVALID_ARG,
                 "opts->sweep 2 (rotated) needs kernel 1, or kernel 3 with mask_mode 2, as one launch of "
                 "one-slice chunks (schedule 1)");
-  p->rotate = o.sweep == 2 || (o.sweep == 0 && can_rotate);
+  // (small batches: every phase of the larger tiles that they stand in for is 0)
+  p->rotate = (o.sweep == 2 || (o.sweep == 0 && can_rotate)) && !small;
   p->nunits = (B + p->D - 1) / p->D;
   if (p->nunits >= kMaxTiles)
     return fail(SOM_ERR_INVALID_ARG, "batch too large for one launch: too many tiles or groups");
@@ -243,23 +242,25 @@ size_t take(size_t& o, size_t bytes) {
 // positions [nnz]; kernel 3: features [nnz + pad], masks [nnz + pad][D / 32],
 // pad = 256 entries, plus 16 per tile with stage masks.
 struct PlanLayout {
-  size_t offset, count, feat, extra, start, total;
+  size_t offset, count, feat, extra, start, super, total;
 };
 
 // List plan (see launch_list_plan), inside the bytes of the automatic kernel's
 // own plan.
 int64_t list_tiles(int64_t B, int docs) { return (B + som::kListWaves * docs - 1) / (som::kListWaves * docs); }
 
-PlanLayout list_layout(int64_t B, int64_t nnz, int docs) {
+PlanLayout list_layout(int64_t B, int64_t nnz, int docs, int form) {
   PlanLayout l{};
+  const bool super = form == som::kListSuperOrder;
   const int64_t nt = list_tiles(B, docs);
   const int64_t caps = nnz / som::kListRows + nt;   // each tile's nonzeros, rounded up
   size_t o = 0;
   l.offset = take(o, sizeof(int32_t) * (nt + 1));
   l.count = take(o, sizeof(int32_t) * nt);
   // the search reads whole 32-byte groups at the start of a list whatever its length
-  l.feat = take(o, static_cast<size_t>(caps) * som::kListCapBytes + 256);
-  l.start = take(o, sizeof(uint32_t) * (caps * som::kListWaves + nt + 4));
+  l.feat = take(o, static_cast<size_t>(caps) * som::list_cap_bytes(super) + 256);
+  l.start = take(o, sizeof(uint32_t) * (caps * som::list_cap_lists(super) + nt + 4));
+  if (super) l.super = take(o, sizeof(int32_t) * ((B + som::kListSuper - 1) / som::kListSuper + 1));
   l.total = o;
   return l;
 }
@@ -279,28 +280,38 @@ PlanLayout plan_layout(const Plan& p, int64_t nnz) {
   return l;
 }
 
-// The automatic launch takes the list form of the shared-union search (tiles of
-// 256 documents for fp32, 128 for fp16) wherever its plan fits the bytes of the
-// kernel it stands in for (so buffer sizes do not depend on the choice), from
-// kListMinDocs documents on: below, too few workgroups fill the device (a
-// 2,048-document fp32 batch took 0.53 ms on the 128^2 map and 1.79 ms on 256^2
-// against kernel 3's 0.74 and 2.19; 1,024 documents 0.52 and 1.79 against 0.48
-// and 1.25; fp16, against kernel 1, 1,024 documents 0.20 and 0.60 against 0.23
-// and 0.68, 512 documents 0.19 and 0.58 against 0.16 and 0.43).  The choice
-// depends on the batch and F only, not on N, so that a plan serves any codebook
-// and column ranges of one compose exactly.  Any kernel or geometry knob keeps
-// the named kernel.
-constexpr int64_t kListMinDocsF32 = kSmallDocsF32, kListMinDocsF16 = 1024;
+// The automatic launch takes the list form of the shared-union search wherever
+// its plan fits the bytes of the kernel it stands in for (so buffer sizes do not
+// depend on the choice):
+//   fp32, tiles of 256 documents, from kListMinDocs documents on (below, too few
+//     workgroups fill the device: a 2,048-document batch took 0.53 ms on the 128^2
+//     map and 1.79 ms on 256^2 against kernel 3's 0.74 and 2.19, 1,024 documents
+//     0.52 and 1.79 against 0.48 and 1.25).  Up to kListOwnOrderDocs documents it
+//     sums in kernel 3's order (the same bits), from there on in the order that
+//     is fastest for it, with the dense rows first;
+//   fp16, tiles of 128 documents, from kListOwnOrderDocs documents on, in its own
+//     order (kernel 1 below: its eight-document tiles each have a phase).
+// Sums in another order swap about 2.5 units per million documents (fp16: 0.7),
+// over maps of 900 to 262,144 neurons, the three workload laws and both codebooks,
+// and in a few batches some times more; in small batches that can be more than one
+// document in 10,000 (23 of 9,337 drawn batches, the largest of 18,623 documents,
+// and 3 units of one of 32,877), from kListOwnOrderDocs on it was 4e-5 at most.
+// The choice depends on the batch and F only, not on N, so that a plan serves any
+// codebook and column ranges of one compose exactly.  Any kernel or geometry knob
+// keeps the named kernel.
+constexpr int64_t kListMinDocs = 1536, kListOwnOrderDocs = 65536;
 
 void choose_lists(int64_t F, int64_t B, int64_t nnz, const som_bmu_opts* opts, int auto_weights, Plan* p) {
   som_bmu_opts o{};
   if (opts) o = *opts;
   if (!no_geometry(o)) return;
   const bool f16 = auto_weights == som::kWeightsF16;
-  if (F > som::kListMaxF || B < (f16 ? kListMinDocsF16 : kListMinDocsF32)) return;
+  if (F > som::kListMaxF || B < (f16 ? kListOwnOrderDocs : kListMinDocs)) return;
   const int docs = f16 ? 16 : 32;
-  if (list_layout(B, nnz, docs).total > plan_layout(*p, nnz).total) return;
+  const int form = !p->rotate ? som::kListPlain : B < kListOwnOrderDocs ? som::kListSuperOrder : som::kListDense;
+  if (list_layout(B, nnz, docs, form).total > plan_layout(*p, nnz).total) return;
   p->list_docs = docs;
+  p->list_form = form;
 }
 
 // Packed keys: best [B] then second best [B] (the second array is used by
@@ -349,16 +360,16 @@ som_status run_validate(const int32_t* indptr, const int32_t* indices, int64_t B
 
 // Where the plan's arrays lie for the chosen form.
 PlanLayout used_layout(const Plan& p, int64_t B, int64_t nnz) {
-  return p.list_docs ? list_layout(B, nnz, p.list_docs) : plan_layout(p, nnz);
+  return p.list_docs ? list_layout(B, nnz, p.list_docs, p.list_form) : plan_layout(p, nnz);
 }
 
 hipError_t build_plan(const int32_t* indptr, const int32_t* indices, int64_t B, int64_t F,
                       const int32_t* perm, const Plan& p, void* plan, const PlanLayout& l,
                       hipStream_t stream) {
   if (p.list_docs)
-    return som::launch_list_plan(indptr, indices, B, F, perm, p.list_docs, p.rotate, at<int32_t>(plan, l.offset),
+    return som::launch_list_plan(indptr, indices, B, F, perm, p.list_docs, p.list_form, at<int32_t>(plan, l.offset),
                                  at<int32_t>(plan, l.count), at<unsigned char>(plan, l.feat),
-                                 at<uint32_t>(plan, l.start), stream);
+                                 at<uint32_t>(plan, l.start), at<int32_t>(plan, l.super), stream);
   if (p.kernel == 1 || p.kernel == 3)
     return som::launch_tile_plan(indptr, indices, B, F, perm, static_cast<int>(p.D), at<int32_t>(plan, l.offset),
                                  at<int32_t>(plan, l.count), at<int32_t>(plan, l.feat),
@@ -397,6 +408,7 @@ som_status run_planned(const void* W, int weights, int64_t F, int64_t N, int64_t
   a.schedule = p.schedule;
   if (p.list_docs) {
     a.kernel = 4;
+    if (p.list_form == som::kListSuperOrder) a.rotate = 2;
     a.T = p.list_docs;
     a.ntiles = list_tiles(B, p.list_docs);
     a.tile_offset = at<int32_t>(plan, l.offset);

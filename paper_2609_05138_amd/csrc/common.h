@@ -60,38 +60,60 @@ hipError_t launch_tile_plan(const int32_t* indptr, const int32_t* indices, int64
 
 // List plan (for the list form of the shared-union search, search_list.h), in
 // tiles of kListWaves * DW documents: a tile's feature union in ascending order,
-// cut into stages of kListRows, and per (stage, wave) a list of 16-bit entries,
-// one per membership: the document's place in the wave in the low bits, the
-// row's slot offset (a multiple of kListRowBytes) above; padded to whole units
-// of four.  Rows that at least 3/8 of a 256-document tile's documents hold (its
-// dense rows, where there are kListDenseMin of them or more, at most kListRows;
-// rotated sweeps only, since they break the ascending order) come before the
-// others and have no entries: each document has a 64-bit mask of those it holds.
+// cut into stages of kListRows, and per (visit of a stage, wave) a list of 16-bit
+// entries, one per membership: the document's place in the wave in the low bits,
+// the row's slot offset (a multiple of kListRowBytes) above; padded to whole units
+// of four.  Three forms, which fix the order the search sums in:
+//   kListPlain       one visit per stage, swept in ascending order (or, without
+//                    dense rows, from the search's own phase)
+//   kListDense       rows that at least 3/8 of a 256-document tile's documents
+//                    hold (its dense rows, where there are kListDenseMin of them
+//                    or more, at most kListRows) come before the others and have
+//                    no entries: each document has a 64-bit mask of those it
+//                    holds.  Swept from the search's own phase
+//   kListSuperOrder  256-document tiles, summed as kernel 3 sums the four
+//                    64-document super-tiles they hold: a document's rows from
+//                    its super-tile's first feature (rotated sweep) on, then those
+//                    before it.  The sweep starts at a stage q0 and makes nv
+//                    visits, wrapping round, at most twice the stages: one turn,
+//                    and on to the last super-tile's first row.  `super` (the
+//                    exclusive scan of the super-tiles' nonzeros, rounded up to 16)
+//                    is scratch of the plan's making
 // Space is counted in stage capacities: ceil(nnz / kListRows) per tile
 // bound its stages (a union row has a nonzero); tile_offset is their exclusive
-// scan, tile_count the stages in use, and in its upper half the dense rows.  A
-// tile's bytes in `data` start at tile_offset * kListCapBytes: with dense rows
+// scan; tile_count the stages in use, and above them (bit 16 on) the dense rows,
+// or (kListSuperOrder: from bits 11 and 21 on) q0 and nv less the stages.  A
+// tile's bytes in `data` start at tile_offset * list_cap_bytes: with dense rows
 // its documents' masks (eight bytes each, no more than the dense rows' entries
-// would take), the ids of its stages (int32, padded with 0), then its lists.  Its words of `start` begin at tile_offset * kListWaves + t:
-// the start of list i = stage * kListWaves + wave, in units from the tile's
-// first list; list i + 1 follows.
+// would take), the ids of its stages (int32, padded with 0), then its lists.  Its
+// words of `start` begin at tile_offset * list_cap_lists + t: the start of list
+// i = visit * kListWaves + wave, in units from the tile's first list; list i + 1
+// follows.
 constexpr int kListWaves = 8;
 constexpr int kListRows = 64;
 constexpr int kListRowBytes = 512;
-constexpr int kListCapBytes = kListRows * (4 + 2) + kListWaves * 3 * 2;
+enum ListForm { kListPlain = 0, kListDense = 1, kListSuperOrder = 2 };
+constexpr int kListSuper = 64;       // documents of a kernel-3 super-tile
+// per stage: lists, and bytes of ids, entries and the lists' padding
+__host__ __device__ constexpr int list_cap_lists(bool super_order) { return kListWaves * (super_order ? 2 : 1); }
+__host__ __device__ constexpr int list_cap_bytes(bool super_order) {
+  return kListRows * (4 + 2) + list_cap_lists(super_order) * 3 * 2;
+}
 constexpr int kListStageWork = 128;  // a stage's fixed cost in entries, for the phase of rotated sweeps
 constexpr int kListPhaseWgs = 96;    // phase period in workgroups per XCD
 constexpr int64_t kListMaxF = 65536;  // the plan kernel's tables fit the LDS
+static_assert(kListMaxF / kListRows <= 1024, "a tile's stages fit the fields of its count");
 constexpr int kListDenseShare = 3;            // a dense row's holders: eighths of the documents
 constexpr int kListDenseMin = 16;
 constexpr int64_t kListDenseMaxF = 32768;     // the plan kernel's counts fit the LDS
 // masks: kListWaves * DW * 8 bytes; entries saved: kListDenseMin rows of
 // kListWaves * DW * kListDenseShare / 8 entries of 2 bytes
 static_assert(kListDenseMin * 2 * kListDenseShare >= 8 * 8, "the masks fit the space of the entries they replace");
-static_assert(kListCapBytes % 16 == 0, "a tile's ids are read 16 bytes at a time");
+static_assert(list_cap_bytes(false) % 16 == 0 && list_cap_bytes(true) % 16 == 0,
+              "a tile's ids are read 16 bytes at a time");
 hipError_t launch_list_plan(const int32_t* indptr, const int32_t* indices, int64_t B, int64_t F,
-                            const int32_t* perm, int DW, bool dense, int32_t* tile_offset, int32_t* tile_count,
-                            unsigned char* data, uint32_t* start, hipStream_t stream);
+                            const int32_t* perm, int DW, int form, int32_t* tile_offset, int32_t* tile_count,
+                            unsigned char* data, uint32_t* start, int32_t* super, hipStream_t stream);
 
 // Document-group plan (for the documents-on-lanes search): per group of D
 // consecutive documents of the tiled order, the sorted feature union and the
@@ -154,7 +176,8 @@ struct SearchArgs {
   int32_t chunk_slices = 1;
   // kernels 1 and 3 (one launch of one-slice chunks; kernel 3
   // document-major): 1 = rotated sweep; phase_wgs is its phase period, in
-  // workgroups (kernel 3) or tiles (kernel 1) per XCD, set by the launch
+  // workgroups (kernel 3) or tiles (kernel 1) per XCD, set by the launch.  List
+  // form: 1 = from the launch's own phase, 2 = a kListSuperOrder plan
   int32_t rotate = 0;
   int32_t phase_wgs = 0;
   float* score = nullptr;  // unfused comparator: distances of tiled-order documents

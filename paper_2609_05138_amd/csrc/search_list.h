@@ -31,10 +31,12 @@
 // the staged ones are in flight together), and scalar copies of the next list's
 // first entries instead of loading them inside the list's own statement.
 //
-// Sweep order: as kernel 3's rotated sweep (see search_st.h), with the phase
-// taken in work (list entries and rows), or ascending; either way a
-// document's dot product is summed in the sweep's order, one fp32 add per
-// feature, so the ascending sweep gives every kernel's bits.
+// Sweep order, fixed by the plan's form (common.h) and the launch: ascending; as
+// kernel 3's rotated sweep (see search_st.h) from a phase of the tile's own, taken
+// in work (list entries and rows); or kernel 3's very order, super-tile by
+// super-tile.  Each way a document's dot product is summed in the sweep's order,
+// one fp32 add per feature, so the ascending sweep gives every kernel's bits and
+// the last one kernel 3's.
 #pragma once
 
 #include <type_traits>
@@ -439,22 +441,26 @@ k_search_list(SearchArgs a) {
   typedef const __attribute__((address_space(4))) int32_t* const_i32;
   typedef const __attribute__((address_space(4))) char* const_char;
   const int64_t cap0 = ((const_i32)a.tile_offset)[t];
-  const int32_t nst = ((const_i32)a.tile_count)[t] & 0xffff;   // stages
-  const int32_t nd = ((const_i32)a.tile_count)[t] >> 16;       // dense rows
-  // unit offsets of the tile's lists, stage by stage: list (q, w) holds units
-  // pt[q * S + w] .. pt[q * S + w + 1]
-  const const_u32 pt = (const_u32)(a.list_start + cap0 * S + t);
-  const unsigned char* masks = a.list_data + cap0 * kListCapBytes;
+  const uint32_t tc = static_cast<uint32_t>(((const_i32)a.tile_count)[t]);
+  const bool super_order = a.rotate == 2;
+  const int32_t nst = static_cast<int32_t>(tc & 0x7ffu);                      // stages
+  const int32_t nd = super_order ? 0 : static_cast<int32_t>(tc >> 16);        // dense rows
+  // visits of stages: one each, and (kListSuperOrder) some again
+  const int32_t visits = nst + (super_order ? static_cast<int32_t>(tc >> 21) : 0);
+  // unit offsets of the tile's lists, visit by visit: list (v, w) holds units
+  // pt[v * S + w] .. pt[v * S + w + 1]
+  const const_u32 pt = (const_u32)(a.list_start + cap0 * list_cap_lists(super_order) + t);
+  const unsigned char* masks = a.list_data + cap0 * list_cap_bytes(super_order);
   const unsigned char* data = masks + (nd ? S * DW * 8 : 0);
   const const_char lists = (const_char)(data + nst * (R * 4));
 
   if (nst > 0) {
-    // Rotated sweep: the tile's phase, as in kernel 3 (the nonzeros of
+    // Rotated sweep: the plan's first stage, or the tile's phase, as in kernel 3 (the nonzeros of
     // the XCD's earlier tiles over a.phase_wgs tiles' mean, mod 1), then the
     // stage that holds this fraction of the tile's own work, a stage counting
     // as kListStageWork entries beside those it holds.
-    int32_t q = 0;
-    if (a.rotate && nst > 1) {
+    int32_t q = super_order ? static_cast<int32_t>(tc >> 11 & 0x3ffu) : 0;
+    if (a.rotate == 1 && nst > 1) {
       const int64_t first = static_cast<int64_t>(blockIdx.x % kXcds) * per_xcd;
       const int64_t end = first + per_xcd < a.ntiles ? first + per_xcd : a.ntiles;
       const uint64_t o_first = static_cast<uint32_t>(((const_i32)a.tile_offset)[first]);
@@ -493,17 +499,22 @@ k_search_list(SearchArgs a) {
     const const_char starts = (const_char)(pt + wave);
     auto load_range = [&](uint32_t sb) { return *(const __attribute__((address_space(4))) u32x2v*)(starts + sb); };
     const uint32_t end = static_cast<uint32_t>(nst) * kStarts;
+    const uint32_t vend = static_cast<uint32_t>(visits) * kStarts;
     auto after = [&](uint32_t sb) { return sb + kStarts == end ? 0u : sb + kStarts; };
+    auto after_visit = [&](uint32_t vb) { return vb + kStarts == vend ? 0u : vb + kStarts; };
 
-    // offsets in the list starts: the next stage's, and the one after
+    // offsets in the list starts, of a stage (for its ids) and of a visit: the
+    // next one's, and the one after (past the last visit: loaded, not used)
     uint32_t sb = static_cast<uint32_t>(q) * kStarts;
+    uint32_t vb = super_order ? 0u : sb;
     i32x4v id = load_ids(sb);
     issue(id, 0);
-    u32x2v cur = load_range(sb);
+    u32x2v cur = load_range(vb);
     u32x8v set = *(const __attribute__((address_space(4))) u32x8v*)(lists + cur.x * 8u);
     sb = after(sb);
+    vb = after_visit(vb);
     id = load_ids(sb);
-    u32x2v next = load_range(sb);
+    u32x2v next = load_range(vb);
     const uint32_t vl0 = ring0 | static_cast<uint32_t>(lane * 8);
     const uint32_t vm = 0xfe00u;
     const uint64_t lb = reinterpret_cast<uint64_t>((const char*)lists);
@@ -521,8 +532,9 @@ k_search_list(SearchArgs a) {
       lds_barrier();  // the stage is visible to all waves; every wave is done with the stage before
       if (more) issue(id, kSlot - slot);
       sb = after(sb);
+      vb = after_visit(vb);
       id = load_ids(sb);
-      const u32x2v next2 = load_range(sb);
+      const u32x2v next2 = load_range(vb);
       if constexpr (DW == 32)
         if (nd && sbc == 0 && !none)
           add_dense<WT, NPL>(acc, ring, slot + lane * 8, nd, masks + wave * DW * 8, lane);
@@ -532,7 +544,7 @@ k_search_list(SearchArgs a) {
       cur = next;
       next = next2;
     };
-    for (int32_t left = nst; left > 0; left -= 2) {   // stages from this one on
+    for (int32_t left = visits; left > 0; left -= 2) {   // visits from this one on
       step(std::false_type{}, left > 1, false);
       step(std::true_type{}, left > 2, left == 1);
     }

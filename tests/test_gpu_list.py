@@ -1,6 +1,7 @@
 """GPU checks of the automatic launch's list form (tiles of 256 documents for
 fp32, 128 for fp16; per-wave entry lists) at the sizes where it can go wrong:
-the batch size it starts at and ragged last tiles, unions of one stage and of
+the batch sizes its forms start at (fp32: 1,536 documents, in kernel 3's order, and
+65,536, in its own; fp16: 65,536) and ragged last tiles, unions of one stage and of
 one row more, documents with no feature and with more than two 64-lane reads of
 them, maps around the slice width, the largest vocabulary it takes, rows of 4 GB
 and more, and plans searched with the other storage type.
@@ -22,7 +23,15 @@ else:  # collected on CPU-only machines, never run there
     som = None
 
 DEV = "cuda:0"
-MIN_DOCS = {np.float32: 1536, np.float16: 1024}   # batches from which the list form is taken
+# batches from which a form of the list kernel is taken
+FORMS = [(np.float32, 1536), (np.float32, 65536), (np.float16, 65536)]
+
+
+def _csr(key, B, F):
+    """CSR tensors of the distinct (document, feature) pairs in key = document * F + feature."""
+    key = np.unique(key)
+    indptr = np.concatenate([[0], np.cumsum(np.bincount(key // F, minlength=B))])
+    return (torch.from_numpy(indptr.astype(np.int32)).to(DEV), torch.from_numpy((key % F).astype(np.int32)).to(DEV))
 
 
 def _docs(rng, B, F):
@@ -31,14 +40,12 @@ def _docs(rng, B, F):
     n = np.minimum(rng.poisson(min(12, F / 2), B), F)
     n[::37] = 0
     n[1::101] = min(F, 300)
-    rows = []
-    for k in n:
-        ids = rng.choice(F, k, replace=False) if k > F // 4 else np.unique(
-            np.minimum((F * rng.random(k) ** 3).astype(np.int64), F - 1))
-        rows.append(np.sort(ids))
-    indptr = np.concatenate([[0], np.cumsum([len(r) for r in rows])])
-    return (torch.from_numpy(indptr.astype(np.int32)).to(DEV),
-            torch.from_numpy(np.concatenate(rows).astype(np.int32)).to(DEV))
+    short = n <= F // 4
+    doc = np.repeat(np.arange(B, dtype=np.int64)[short], n[short])
+    keys = [doc * F + np.minimum((F * rng.random(doc.size) ** 3).astype(np.int64), F - 1)]
+    for d in np.flatnonzero(~short):                      # exactly n[d] distinct features
+        keys.append(d * F + rng.choice(F, n[d], replace=False))
+    return _csr(np.concatenate(keys), B, F)
 
 
 def _book(rng, F, N, dtype, ldw=None, dyadic=True):
@@ -53,12 +60,12 @@ def _equal(a, b):
     return all(torch.equal(x, y) for x, y in zip(a, b))
 
 
-@pytest.mark.parametrize("dtype", [np.float32, np.float16])
+@pytest.mark.parametrize("dtype,least", FORMS)
 @pytest.mark.parametrize("extra,F,N", [(-1, 300, 200), (0, 64, 128), (1, 65, 127), (255, 2000, 129), (256, 64, 1),
                                        (300, 65536, 300), (130, 5000, 513), (1000, 1, 2)])
-def test_list_form_matches_kernel_1(dtype, extra, F, N):
+def test_list_form_matches_kernel_1(dtype, least, extra, F, N):
     rng = np.random.default_rng(F * 1000 + N)
-    B = MIN_DOCS[dtype] + extra
+    B = least + extra
     ip, ix = _docs(rng, B, F)
     perm = som.som_cluster_order(ip, ix, F)
     W, norms = _book(rng, F, N, dtype)
@@ -71,9 +78,10 @@ def test_list_form_matches_kernel_1(dtype, extra, F, N):
 
 
 @pytest.mark.parametrize("dtype", [np.float32, np.float16])
-def test_list_form_ascending_bits_and_reuse_of_a_plan(dtype):
+@pytest.mark.parametrize("B", [6000, 66000])
+def test_list_form_ascending_bits_and_reuse_of_a_plan(dtype, B):
     rng = np.random.default_rng(7)
-    F, N, B = 3000, 1000, 6000
+    F, N = 3000, 1000
     ip, ix = _docs(rng, B, F)
     perm = som.som_cluster_order(ip, ix, F)
     W, norms = _book(rng, F, N, dtype, dyadic=False)
@@ -95,9 +103,10 @@ def test_list_form_ascending_bits_and_reuse_of_a_plan(dtype):
 
 
 @pytest.mark.parametrize("dtype", [np.float32, np.float16])
-@pytest.mark.parametrize("B", [1, 2, 3, 700, 767, 768, 1023])
+@pytest.mark.parametrize("B", [1, 2, 3, 64, 65, 512, 513, 700, 767, 768, 1023])
 def test_small_batches_match_kernel_1(dtype, B):
-    # below the list form: two-document tiles of kernel 1 (fp16 up to 767)
+    # two-document tiles of kernel 1 (up to 512 documents, fp16 64), and the
+    # kernels between them and the list form
     rng = np.random.default_rng(B)
     F, N = 900, 700
     ip, ix = _docs(rng, B, F)
@@ -120,19 +129,20 @@ def test_list_form_rows_of_4_gib():
     assert _equal(som.som_bmu_search(W, norms, ip, ix, N=N), want[:2])
 
 
-@pytest.mark.parametrize("dtype", [np.float32, np.float16])
+@pytest.mark.parametrize("dtype,least", FORMS)
 @pytest.mark.parametrize("dense,share,F", [(15, 0.5, 400), (16, 0.4, 400), (17, 1.0, 32768), (64, 0.3, 65), (63, 0.3, 300),
                                            (100, 0.5, 3000), (40, 0.25, 500), (64, 1.0, 64), (40, 0.5, 32769)])
-def test_rows_that_many_documents_hold(dtype, dense, share, F):
-    # such rows of a tile (from 16 of them on, at most 64) are summed on the matrix cores
+def test_rows_that_many_documents_hold(dtype, least, dense, share, F):
+    # such rows of a tile (from 16 of them on, at most 64) are summed on the matrix
+    # cores (fp32, from 65,536 documents on)
     rng = np.random.default_rng(dense * 7 + F)
-    B, N = MIN_DOCS[dtype] + 300, 300
+    B, N = least + 300, 300
     hot = np.sort(rng.choice(F, dense, replace=False))
-    rows = [np.unique(np.concatenate([hot[rng.random(dense) < share], rng.integers(0, F, rng.integers(0, 9))]))
-            for _ in range(B)]
-    rows[5] = rows[-1] = np.zeros(0, np.int64)
-    ip = torch.from_numpy(np.concatenate([[0], np.cumsum([len(r) for r in rows])]).astype(np.int32)).to(DEV)
-    ix = torch.from_numpy(np.concatenate(rows).astype(np.int32)).to(DEV)
+    at = np.flatnonzero(rng.random(B * dense) < share)
+    doc = np.repeat(np.arange(B, dtype=np.int64), rng.integers(0, 9, B))
+    key = np.concatenate([at // dense * F + hot[at % dense], doc * F + rng.integers(0, F, doc.size)])
+    key = key[(key // F != 5) & (key // F != B - 1)]
+    ip, ix = _csr(key, B, F)
     W, norms = _book(rng, F, N, dtype)
     for special in (False, True):
         if special:   # 0 times an infinity or a NaN is no 0; finite norms, so that they show
