@@ -379,20 +379,9 @@ hipError_t build_plan(const int32_t* indptr, const int32_t* indices, int64_t B, 
                                 at<int32_t>(plan, l.feat), at<int32_t>(plan, l.extra), stream);
 }
 
-som_status run_planned(const void* W, int weights, int64_t F, int64_t N, int64_t ldw, const float* norms,
-                       const int32_t* indptr, int64_t B, const int32_t* perm, const void* plan,
-                       const PlanLayout& l, int32_t* bmu, float* dist, int32_t* bmu2, float* dist2,
-                       const Plan& p, uint64_t* keys, hipStream_t stream) {
-  som::SearchArgs a{};
-  a.W = W;
-  a.weights = weights;
-  a.F = F;
-  a.N = N;
-  a.ldw = ldw;
-  a.norms = norms;
-  a.indptr = indptr;
-  a.perm = perm;
-  a.B = B;
+// The kernel that `p` names, its geometry and its plan's arrays.
+void plan_args(const Plan& p, const void* plan, const PlanLayout& l, som::SearchArgs* args) {
+  som::SearchArgs& a = *args;
   a.kernel = p.kernel;
   a.T = p.T;
   a.K = p.K;
@@ -410,7 +399,7 @@ som_status run_planned(const void* W, int weights, int64_t F, int64_t N, int64_t
     a.kernel = 4;
     if (p.list_form == som::kListSuperOrder) a.rotate = 2;
     a.T = p.list_docs;
-    a.ntiles = list_tiles(B, p.list_docs);
+    a.ntiles = list_tiles(a.B, p.list_docs);
     a.tile_offset = at<int32_t>(plan, l.offset);
     a.tile_count = at<int32_t>(plan, l.count);
     a.list_data = at<unsigned char>(plan, l.feat);
@@ -426,6 +415,26 @@ som_status run_planned(const void* W, int weights, int64_t F, int64_t N, int64_t
     a.group_feat = at<int32_t>(plan, l.feat);
     a.entry_pos = at<int32_t>(plan, l.extra);
   }
+}
+
+// `other`: the plan may be of its kind instead; both kernels are launched, and the
+// one whose kind the plan is not ends at once.
+som_status run_planned(const void* W, int weights, int64_t F, int64_t N, int64_t ldw, const float* norms,
+                       const int32_t* indptr, int64_t B, const int32_t* perm, const void* plan,
+                       const PlanLayout& l, int32_t* bmu, float* dist, int32_t* bmu2, float* dist2,
+                       const Plan& p, uint64_t* keys, hipStream_t stream,
+                       const Plan* other = nullptr, const PlanLayout* other_l = nullptr) {
+  som::SearchArgs a{};
+  a.W = W;
+  a.weights = weights;
+  a.F = F;
+  a.N = N;
+  a.ldw = ldw;
+  a.norms = norms;
+  a.indptr = indptr;
+  a.perm = perm;
+  a.B = B;
+  plan_args(p, plan, l, &a);
   a.keys = keys;
   a.bmu = bmu;
   a.dist = dist;
@@ -434,7 +443,12 @@ som_status run_planned(const void* W, int weights, int64_t F, int64_t N, int64_t
     a.bmu2 = bmu2;
     a.dist2 = dist2;
   }
+  a.either = other ? 1 : 0;
   hipError_t e = som::launch_search(a, stream);
+  if (e == hipSuccess && other) {
+    plan_args(*other, plan, *other_l, &a);
+    e = som::launch_kernel(a, stream);
+  }
   if (e != hipSuccess) return hip_fail(e, "search launch");
   e = som::launch_merge(a, stream);
   if (e != hipSuccess) return hip_fail(e, "decode launch");
@@ -703,9 +717,14 @@ static som_status planned_impl(const void* W, int weights, int64_t F, int64_t N,
   if (!aligned(ws, 256)) return fail(SOM_ERR_INVALID_ARG, "ws must be 256-byte aligned");
   if (ws_bytes < keys_bytes(B))
     return fail(SOM_ERR_WORKSPACE, "workspace too small: need " + std::to_string(keys_bytes(B)) + " bytes");
-  choose_lists(F, B, nnz, opts, opts_storage(opts), &p);
-  return run_planned(W, weights, F, N, ldw, norms, indptr, B, perm, plan, used_layout(p, B, nnz), bmu, dist, top2 ? bmu2 : nullptr, dist2,
-                     p, static_cast<uint64_t*>(ws), stream);
+  // the form som_plan chose: its F is at most this one, so up to kListMaxF both
+  // choices agree; beyond, the plan may be a list plan (of a smaller F) or not
+  Plan q = p;
+  choose_lists(F < som::kListMaxF ? F : som::kListMaxF, B, nnz, opts, opts_storage(opts), &q);
+  const bool either = q.list_docs && F > som::kListMaxF;
+  const PlanLayout ql = used_layout(q, B, nnz);
+  return run_planned(W, weights, F, N, ldw, norms, indptr, B, perm, plan, ql, bmu, dist, top2 ? bmu2 : nullptr, dist2, q,
+                     static_cast<uint64_t*>(ws), stream, either ? &p : nullptr, &l);
 }
 
 som_status som_bmu_search_planned(const float* W, int64_t F, int64_t N, int64_t ldw,

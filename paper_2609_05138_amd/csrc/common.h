@@ -81,7 +81,8 @@ hipError_t launch_tile_plan(const int32_t* indptr, const int32_t* indices, int64
 //                    is scratch of the plan's making
 // Space is counted in stage capacities: ceil(nnz / kListRows) per tile
 // bound its stages (a union row has a nonzero); tile_offset is their exclusive
-// scan; tile_count the stages in use, and above them (bit 16 on) the dense rows,
+// scan, with kListTag set in its first word (a tile plan's, at the same place, is
+// 0), so that a search can tell the plans apart; tile_count the stages in use, and above them (bit 16 on) the dense rows,
 // or (kListSuperOrder: from bits 11 and 21 on) q0 and nv less the stages.  A
 // tile's bytes in `data` start at tile_offset * list_cap_bytes: with dense rows
 // its documents' masks (eight bytes each, no more than the dense rows' entries
@@ -92,6 +93,7 @@ hipError_t launch_tile_plan(const int32_t* indptr, const int32_t* indices, int64
 constexpr int kListWaves = 8;
 constexpr int kListRows = 64;
 constexpr int kListRowBytes = 512;
+constexpr uint32_t kListTag = 0x80000000u;
 enum ListForm { kListPlain = 0, kListDense = 1, kListSuperOrder = 2 };
 constexpr int kListSuper = 64;       // documents of a kernel-3 super-tile
 // per stage: lists, and bytes of ids, entries and the lists' padding
@@ -180,6 +182,9 @@ struct SearchArgs {
   // form: 1 = from the launch's own phase, 2 = a kListSuperOrder plan
   int32_t rotate = 0;
   int32_t phase_wgs = 0;
+  // 1: the launch ends at once unless the plan is of its kernel's kind (list or
+  // tile plan, told apart by kListTag): both kinds are launched, one after the other
+  int32_t either = 0;
   float* score = nullptr;  // unfused comparator: distances of tiled-order documents
                            // [tile_base * T, ...) go to score[(p - tile_base * T) * N + j]
   const int32_t* tile_offset;
@@ -205,7 +210,9 @@ struct SearchArgs {
   float* dist2;
 };
 
+// Initialises the keys, then runs the fused search (launch_kernel: without them).
 hipError_t launch_search(const SearchArgs& a, hipStream_t stream);
+hipError_t launch_kernel(const SearchArgs& a, hipStream_t stream);
 // Kernels 1 and 3 over an fp16 codebook (their own translation unit).
 hipError_t launch_search_k1_f16(const SearchArgs& a, hipStream_t stream);
 hipError_t launch_search_st_f16(const SearchArgs& a, hipStream_t stream);
@@ -213,8 +220,7 @@ hipError_t launch_search_list_f16(const SearchArgs& a, hipStream_t stream);
 // Unfused comparator: kernel 1 writes the distance block of block_docs
 // documents at a time into `score`, then a wave-per-row argmin reduces it.
 hipError_t launch_unfused(SearchArgs a, int64_t block_docs, hipStream_t stream);
-// Initialises the keys, then runs the fused search; launch_merge decodes the
-// keys into results in input order.
+// Decodes the keys into results in input order.
 hipError_t launch_merge(const SearchArgs& a, hipStream_t stream);
 
 // Batch-SOM update (update.hip).

@@ -85,6 +85,7 @@ __global__ void __launch_bounds__(1024)
 k_list_scan(const int32_t* caps, int64_t n, int32_t* tile_offset, int32_t* super, int64_t nsuper) {
   __shared__ int32_t wsum[16];
   list_scan(caps, n, tile_offset, wsum);
+  if (threadIdx.x == 0) tile_offset[0] = static_cast<int32_t>(kListTag);   // 0, and the plan's mark
   if (super) list_scan(super, nsuper, super, wsum);
 }
 
@@ -214,7 +215,7 @@ k_list_plan(const int32_t* __restrict__ indptr, const int32_t* __restrict__ indi
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int64_t t = blockIdx.x;
-  const int64_t cap0 = tile_offset[t];
+  const int64_t cap0 = static_cast<int64_t>(static_cast<uint32_t>(tile_offset[t]) & ~kListTag);
   unsigned char* base = data + cap0 * list_cap_bytes(SUPER);
   int32_t begin = 0, end = 0;
   {

@@ -359,6 +359,10 @@ hipError_t launch_k4(const SearchArgs& a, hipStream_t stream) {
 hipError_t launch_search(const SearchArgs& a, hipStream_t stream) {
   hipLaunchKernelGGL(k_keys_init, dim3(static_cast<uint32_t>((a.B + 255) / 256)), dim3(256), 0, stream,
                      a.keys, a.keys2, a.B);
+  return launch_kernel(a, stream);
+}
+
+hipError_t launch_kernel(const SearchArgs& a, hipStream_t stream) {
   if (a.kernel == 2) return launch_docs(a, stream);
   if (a.kernel == 3) return launch_k3(a, stream);
   if (a.kernel == 4) return launch_k4(a, stream);

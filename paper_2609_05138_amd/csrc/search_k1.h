@@ -295,6 +295,7 @@ k_search(SearchArgs a) {
   static_assert(K % E == 0 && K % 4 == 0, "a lane holds whole 128-bit loads");
   static_assert(kEntryChunk % (2 * U) == 0, "row batches must tile a window");
   __shared__ int2 ent_all[G][kEntryChunk + 2 * U];
+  if (a.either && (static_cast<uint32_t>(a.tile_offset[0]) & kListTag)) return;  // a list plan
 
   const int lane = threadIdx.x & 63;
   const int wave = threadIdx.x >> 6;

@@ -421,6 +421,7 @@ k_search_list(SearchArgs a) {
   const uint32_t per_xcd = gridDim.x / kXcds;
   const int64_t t = static_cast<int64_t>(blockIdx.x % kXcds) * per_xcd + blockIdx.x / kXcds;
   if (t >= a.ntiles) return;  // whole workgroup: no barrier is skipped by part of it
+  if (a.either && !(static_cast<uint32_t>(a.tile_offset[0]) & kListTag)) return;  // a tile plan
   const int64_t n0 = (a.slice_base + blockIdx.y) * WN;
 
   ListAcc<DW, NPL> acc;
@@ -440,7 +441,10 @@ k_search_list(SearchArgs a) {
   typedef const __attribute__((address_space(4))) uint32_t* const_u32;
   typedef const __attribute__((address_space(4))) int32_t* const_i32;
   typedef const __attribute__((address_space(4))) char* const_char;
-  const int64_t cap0 = ((const_i32)a.tile_offset)[t];
+  auto offset = [&](int64_t i) {
+    return static_cast<uint64_t>(static_cast<uint32_t>(((const_i32)a.tile_offset)[i]) & ~kListTag);
+  };
+  const int64_t cap0 = static_cast<int64_t>(offset(t));
   const uint32_t tc = static_cast<uint32_t>(((const_i32)a.tile_count)[t]);
   const bool super_order = a.rotate == 2;
   const int32_t nst = static_cast<int32_t>(tc & 0x7ffu);                      // stages
@@ -463,8 +467,8 @@ k_search_list(SearchArgs a) {
     if (a.rotate == 1 && nst > 1) {
       const int64_t first = static_cast<int64_t>(blockIdx.x % kXcds) * per_xcd;
       const int64_t end = first + per_xcd < a.ntiles ? first + per_xcd : a.ntiles;
-      const uint64_t o_first = static_cast<uint32_t>(((const_i32)a.tile_offset)[first]);
-      const uint64_t work = static_cast<uint32_t>(((const_i32)a.tile_offset)[end]) - o_first;  // > 0
+      const uint64_t o_first = offset(first);
+      const uint64_t work = offset(end) - o_first;                 // > 0
       const uint64_t den = static_cast<uint64_t>(a.phase_wgs) * work;
       const uint64_t num = (static_cast<uint64_t>(cap0) - o_first) * static_cast<uint64_t>(end - first) % den;
       const uint64_t ph = (num << 20) / den;                       // phase in 2^-20

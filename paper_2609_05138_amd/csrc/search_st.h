@@ -166,6 +166,7 @@ k_search_st(SearchArgs a) {
   constexpr int OPS = RPW + 1;        // loads per wave per stage (rows + mask words)
   __shared__ u32x4 ring[NSLOT][P][64];      // row slices
   __shared__ uint32_t mring[NSLOT][S][64];  // per wave: its mask word of each entry
+  if (a.either && (static_cast<uint32_t>(a.tile_offset[0]) & kListTag)) return;  // a list plan
 
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
