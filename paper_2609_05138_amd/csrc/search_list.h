@@ -319,8 +319,11 @@ __device__ __forceinline__ uint32_t wave_min_u32(uint32_t x) {
 // Distances, argmin (or the two smallest) and key merge of a wave's DW
 // documents over its slice.  Per document the lane's best neuron is reduced
 // over the wave as ordered distance bits; the lowest lane that holds the
-// minimum gives the lowest index (a lane's neurons ascend, and lanes do; columns
-// past the last neuron are +inf, behind every neuron).  Lane s then holds
+// minimum gives the lowest index (a lane's neurons ascend, and lanes do).  Columns
+// past the last neuron are left out by their index, as their accumulators hold
+// whatever lies between the rows: inside a lane they follow its neurons with an
+// infinite or NaN distance, which is never less than another; lanes without a
+// neuron, or (second best) without a second one, take no part.  Lane s then holds
 // document s's key, and one vector compare filters the atomics: a stale read of
 // the stored key only lets a useless update through, as keys only fall.
 template <int DW, int NPL, bool TOP2>
@@ -333,6 +336,8 @@ __device__ __forceinline__ void list_epilogue(const SearchArgs& a, const ListAcc
     const int64_t j = n0 + lane * NPL + q;
     nrm[q] = j < a.N ? a.norms[j] : __builtin_inff();
   }
+  const bool one = n0 + lane * NPL < a.N, two = n0 + lane * NPL + 1 < a.N;   // neurons of this lane
+  const uint64_t ones = __ballot(one), twos = __ballot(two);
   const int64_t p = p0 + lane;
   const bool mine = lane < DW && p < a.B;
   float nnz = 0.f;
@@ -361,18 +366,22 @@ __device__ __forceinline__ void list_epilogue(const SearchArgs& a, const ListAcc
       q1 = lt1 ? static_cast<uint32_t>(q) : q1;
       d1 = lt1 ? d : d1;
     }
-    const uint32_t b1 = ordered_bits(d1);
+    const uint32_t b1 = one ? ordered_bits(d1) : ~0u;
     const uint32_t m = wave_min_u32(b1);
-    const int l = __builtin_ctzll(__ballot(b1 == m));   // some lane holds the minimum
+    const int l = __builtin_ctzll(__ballot(b1 == m));   // some lane holds the minimum; lane 0 has a neuron
     const int j = static_cast<int>(n0) + l * NPL + __builtin_amdgcn_readlane(static_cast<int>(q1), l);
     m1 = lane == s ? static_cast<int>(m) : m1;
     j1 = lane == s ? j : j1;
     if (TOP2) {
-      const uint32_t c = lane == l ? ordered_bits(d2) : b1;
+      const uint32_t c = lane == l ? (two ? ordered_bits(d2) : ~0u) : b1;
       const uint32_t cq = lane == l ? q2 : q1;
       const uint32_t mm = wave_min_u32(c);
-      const int l2 = __builtin_ctzll(__ballot(c == mm));
-      const int jj = static_cast<int>(n0) + l2 * NPL + __builtin_amdgcn_readlane(static_cast<int>(cq), l2);
+      const uint64_t others = (ones & ~(1ull << l)) | (twos & (1ull << l));
+      int jj = -1;   // a slice of one neuron has no second best: m2 = j2 = -1, kNoKey
+      if (others) {
+        const int l2 = __builtin_ctzll(__ballot(c == mm) & others);
+        jj = static_cast<int>(n0) + l2 * NPL + __builtin_amdgcn_readlane(static_cast<int>(cq), l2);
+      }
       m2 = lane == s ? static_cast<int>(mm) : m2;
       j2 = lane == s ? jj : j2;
     }
@@ -384,9 +393,7 @@ __device__ __forceinline__ void list_epilogue(const SearchArgs& a, const ListAcc
     if (k1 < *kb) atomicMin(reinterpret_cast<unsigned long long*>(kb), static_cast<unsigned long long>(k1));
     return;
   }
-  // a slice of one neuron has no second best
-  const uint64_t k2 = a.N - n0 < 2 ? kNoKey
-                                   : (static_cast<uint64_t>(static_cast<uint32_t>(m2)) << 32) | static_cast<uint32_t>(j2);
+  const uint64_t k2 = (static_cast<uint64_t>(static_cast<uint32_t>(m2)) << 32) | static_cast<uint32_t>(j2);
   const uint64_t displaced = k1 < *kb ? top2_displaced(kb, k1) : k1;
   const uint64_t cand = displaced < k2 ? displaced : k2;
   uint64_t* ks = a.keys2 + p;

@@ -155,3 +155,25 @@ def test_rows_that_many_documents_hold(dtype, least, dense, share, F):
             got = som.som_bmu_search_top2(W, norms, ip, ix, N=N, sweep=sweep)
             assert _equal(got, want), (special, sweep)
             assert _equal(som.som_bmu_search(W, norms, ip, ix, N=N, sweep=sweep), want[:2]), (special, sweep)
+
+
+@pytest.mark.parametrize("dtype,least", FORMS)
+@pytest.mark.parametrize("N", [1, 2, 3, 5, 127, 129, 130, 131, 257, 260, 261, 510])
+def test_what_lies_between_the_rows_is_never_a_unit(dtype, least, N):
+    # the columns from N to the row stride hold no neuron: a NaN there whose sign
+    # bit is set would come before every distance
+    rng = np.random.default_rng(N)
+    B, F = least + 77, 200
+    ip, ix = _docs(rng, B, F)
+    W, norms = _book(rng, F, N, dtype)
+    W[:, N:].view(torch.int16 if dtype == np.float16 else torch.int32).fill_(-1)
+    want = som.som_bmu_search_top2(W, norms, ip, ix, N=N, kernel=1, sweep=1)
+    for sweep in (0, 1):
+        assert _equal(som.som_bmu_search_top2(W, norms, ip, ix, N=N, sweep=sweep), want), sweep
+        assert _equal(som.som_bmu_search(W, norms, ip, ix, N=N, sweep=sweep), want[:2]), sweep
+    # where no distance is a number, there is no best unit, but the answer is one of the map
+    for bits in (0x7fc00000, -1):
+        norms.view(torch.int32).fill_(bits)
+        bmu, _, bmu2, _ = som.som_bmu_search_top2(W, norms, ip, ix, N=N)
+        assert 0 <= int(bmu.min()) and int(bmu.max()) < N
+        assert -1 <= int(bmu2.min()) and int(bmu2.max()) < N
