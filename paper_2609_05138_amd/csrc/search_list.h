@@ -408,8 +408,10 @@ constexpr int list_min_waves() {
   return sizeof(WT) == 2 && DW == 32 ? 2 : 4;
 }
 
-// WIDE: codebook rows of 4 GB and more.
-template <typename WT, int DW, bool TOP2, bool WIDE>
+// WIDE: codebook rows of 4 GB and more.  SUPER: a kListSuperOrder plan (a second
+// place in the lists, beside the stages', cost the other forms 0.6% at 512^2: 507.5
+// against 504.3 ms per 262,144 documents).
+template <typename WT, int DW, bool TOP2, bool WIDE, bool SUPER>
 __global__ void __launch_bounds__(kListWaves * 64) __attribute__((amdgpu_waves_per_eu(list_min_waves<WT, DW>())))
 k_search_list(SearchArgs a) {
   constexpr int E = Storage<WT>::kE;                               // elements per 128-bit load
@@ -453,15 +455,14 @@ k_search_list(SearchArgs a) {
   };
   const int64_t cap0 = static_cast<int64_t>(offset(t));
   const uint32_t tc = static_cast<uint32_t>(((const_i32)a.tile_count)[t]);
-  const bool super_order = a.rotate == 2;
   const int32_t nst = static_cast<int32_t>(tc & 0x7ffu);                      // stages
-  const int32_t nd = super_order ? 0 : static_cast<int32_t>(tc >> 16);        // dense rows
+  const int32_t nd = SUPER ? 0 : static_cast<int32_t>(tc >> 16);              // dense rows
   // visits of stages: one each, and (kListSuperOrder) some again
-  const int32_t visits = nst + (super_order ? static_cast<int32_t>(tc >> 21) : 0);
+  const int32_t visits = nst + (SUPER ? static_cast<int32_t>(tc >> 21) : 0);
   // unit offsets of the tile's lists, visit by visit: list (v, w) holds units
   // pt[v * S + w] .. pt[v * S + w + 1]
-  const const_u32 pt = (const_u32)(a.list_start + cap0 * list_cap_lists(super_order) + t);
-  const unsigned char* masks = a.list_data + cap0 * list_cap_bytes(super_order);
+  const const_u32 pt = (const_u32)(a.list_start + cap0 * list_cap_lists(SUPER) + t);
+  const unsigned char* masks = a.list_data + cap0 * list_cap_bytes(SUPER);
   const unsigned char* data = masks + (nd ? S * DW * 8 : 0);
   const const_char lists = (const_char)(data + nst * (R * 4));
 
@@ -470,8 +471,8 @@ k_search_list(SearchArgs a) {
     // the XCD's earlier tiles over a.phase_wgs tiles' mean, mod 1), then the
     // stage that holds this fraction of the tile's own work, a stage counting
     // as kListStageWork entries beside those it holds.
-    int32_t q = super_order ? static_cast<int32_t>(tc >> 11 & 0x3ffu) : 0;
-    if (a.rotate == 1 && nst > 1) {
+    int32_t q = SUPER ? static_cast<int32_t>(tc >> 11 & 0x3ffu) : 0;
+    if (!SUPER && a.rotate && nst > 1) {
       const int64_t first = static_cast<int64_t>(blockIdx.x % kXcds) * per_xcd;
       const int64_t end = first + per_xcd < a.ntiles ? first + per_xcd : a.ntiles;
       const uint64_t o_first = offset(first);
@@ -512,18 +513,18 @@ k_search_list(SearchArgs a) {
     const uint32_t end = static_cast<uint32_t>(nst) * kStarts;
     const uint32_t vend = static_cast<uint32_t>(visits) * kStarts;
     auto after = [&](uint32_t sb) { return sb + kStarts == end ? 0u : sb + kStarts; };
-    auto after_visit = [&](uint32_t vb) { return vb + kStarts == vend ? 0u : vb + kStarts; };
+    auto after_visit = [&](uint32_t vb) { return vb + kStarts == vend ? 0u : vb + kStarts; };   // (SUPER)
 
     // offsets in the list starts, of a stage (for its ids) and of a visit: the
     // next one's, and the one after (past the last visit: loaded, not used)
     uint32_t sb = static_cast<uint32_t>(q) * kStarts;
-    uint32_t vb = super_order ? 0u : sb;
+    uint32_t vb = SUPER ? 0u : sb;
     i32x4v id = load_ids(sb);
     issue(id, 0);
     u32x2v cur = load_range(vb);
     u32x8v set = *(const __attribute__((address_space(4))) u32x8v*)(lists + cur.x * 8u);
     sb = after(sb);
-    vb = after_visit(vb);
+    vb = SUPER ? after_visit(vb) : sb;
     id = load_ids(sb);
     u32x2v next = load_range(vb);
     const uint32_t vl0 = ring0 | static_cast<uint32_t>(lane * 8);
@@ -543,10 +544,10 @@ k_search_list(SearchArgs a) {
       lds_barrier();  // the stage is visible to all waves; every wave is done with the stage before
       if (more) issue(id, kSlot - slot);
       sb = after(sb);
-      vb = after_visit(vb);
+      vb = SUPER ? after_visit(vb) : sb;
       id = load_ids(sb);
       const u32x2v next2 = load_range(vb);
-      if constexpr (DW == 32)
+      if constexpr (DW == 32 && !SUPER)
         if (nd && sbc == 0 && !none)
           add_dense<WT, NPL>(acc, ring, slot + lane * 8, nd, masks + wave * DW * 8, lane);
       sbc = after(sbc);
@@ -563,6 +564,17 @@ k_search_list(SearchArgs a) {
   list_epilogue<DW, NPL, TOP2>(a, acc, t * (S * DW) + wave * DW, n0, lane);
 }
 
+template <typename WT, int DW, bool TOP2, bool WIDE>
+void launch_list_grid(const SearchArgs& a, dim3 grid, hipStream_t stream) {
+  if constexpr (DW == 32) {
+    if (a.rotate == 2) {
+      hipLaunchKernelGGL((k_search_list<WT, DW, TOP2, WIDE, true>), grid, dim3(kListWaves * 64), 0, stream, a);
+      return;
+    }
+  }
+  hipLaunchKernelGGL((k_search_list<WT, DW, TOP2, WIDE, false>), grid, dim3(kListWaves * 64), 0, stream, a);
+}
+
 template <typename WT, int DW>
 hipError_t launch_list(const SearchArgs& a, hipStream_t stream) {
   // grid.y holds at most 65,535 slices: wider maps take several launches
@@ -576,13 +588,13 @@ hipError_t launch_list(const SearchArgs& a, hipStream_t stream) {
     const dim3 grid(static_cast<uint32_t>((a.ntiles + kXcds - 1) / kXcds * kXcds),
                     static_cast<uint32_t>(slices - c < 65535 ? slices - c : 65535));
     if (wide && a.keys2)
-      hipLaunchKernelGGL((k_search_list<WT, DW, true, true>), grid, dim3(kListWaves * 64), 0, stream, b);
+      launch_list_grid<WT, DW, true, true>(b, grid, stream);
     else if (wide)
-      hipLaunchKernelGGL((k_search_list<WT, DW, false, true>), grid, dim3(kListWaves * 64), 0, stream, b);
+      launch_list_grid<WT, DW, false, true>(b, grid, stream);
     else if (a.keys2)
-      hipLaunchKernelGGL((k_search_list<WT, DW, true, false>), grid, dim3(kListWaves * 64), 0, stream, b);
+      launch_list_grid<WT, DW, true, false>(b, grid, stream);
     else
-      hipLaunchKernelGGL((k_search_list<WT, DW, false, false>), grid, dim3(kListWaves * 64), 0, stream, b);
+      launch_list_grid<WT, DW, false, false>(b, grid, stream);
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
   }
