@@ -260,9 +260,7 @@ hipError_t launch_cluster(const int32_t* indptr, const int32_t* indices, int64_t
     const int64_t share = (nnz + kHistGroups - 1) / kHistGroups;
     const int64_t items = share > kHistItems ? share : kHistItems;
     const uint32_t groups = static_cast<uint32_t>((nnz + items - 1) / items);
-    const int lds = static_cast<int>(sizeof(int32_t) * (F < kHistWindow ? F : kHistWindow));
-    const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(k_df_lds),
-                                             hipFuncAttributeMaxDynamicSharedMemorySize, lds);
+    const hipError_t e = allow_lds(&k_df_lds, sizeof(int32_t) * kHistWindow);
     if (e != hipSuccess) return e;
     for (int64_t w0 = 0; w0 < F; w0 += kHistWindow) {
       const int wlen = static_cast<int>(F - w0 < kHistWindow ? F - w0 : kHistWindow);

@@ -28,6 +28,15 @@ __device__ __forceinline__ uint64_t pack_key(float d, uint32_t j) {
 
 constexpr uint64_t kNoKey = ~0ull;
 
+// Lets `kernel` be launched with up to `most` bytes of dynamic LDS.  `most` is the
+// most that any call asks for: the limit belongs to the process, and a call that
+// set it to its own need would lower it under another thread's launch.
+template <typename F>
+hipError_t allow_lds(F* kernel, size_t most) {
+  return hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize,
+                             static_cast<int>(most));
+}
+
 inline size_t align_up(size_t x, size_t a) { return (x + a - 1) / a * a; }
 
 // ---------------------------------------------------------------------------

@@ -290,8 +290,7 @@ hipError_t launch_group_plan(const int32_t* indptr, const int32_t* indices, int6
   hipLaunchKernelGGL(k_scan, dim3(1), dim3(1024), 0, stream, group_count, ngroups, group_offset);
   const int window = static_cast<int>(F < kPlanWindow ? F : kPlanWindow);
   const size_t lds = sizeof(uint32_t) * static_cast<size_t>(window);
-  hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(k_gplan),
-                                     hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(lds));
+  hipError_t e = allow_lds(&k_gplan, sizeof(uint32_t) * kPlanWindow);
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL(k_gplan, dim3(static_cast<uint32_t>(ngroups)), dim3(kPlanThreads), lds, stream,
                      indptr, indices, perm, B, F, D, window, group_offset, group_count, group_feat,
@@ -325,9 +324,7 @@ hipError_t launch_tile_plan(const int32_t* indptr, const int32_t* indices, int64
   const int MW = (T + 31) / 32;
   const int window = static_cast<int>(F < kPlanWindow / MW ? F : kPlanWindow / MW);
   const size_t lds = sizeof(uint32_t) * static_cast<size_t>(window) * MW;
-  hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(k_plan),
-                                     hipFuncAttributeMaxDynamicSharedMemorySize,
-                                     static_cast<int>(lds));
+  hipError_t e = allow_lds(&k_plan, sizeof(uint32_t) * kPlanWindow);
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL(k_plan, dim3(static_cast<uint32_t>(ntiles)), dim3(kPlanThreads), lds, stream,
                      indptr, indices, perm, B, F, T, MW, window, tile_offset, tile_count, union_feat,

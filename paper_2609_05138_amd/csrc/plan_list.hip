@@ -425,6 +425,13 @@ k_list_plan(const int32_t* __restrict__ indptr, const int32_t* __restrict__ indi
     for (int32_t k = list[i]; k & 3; ++k) entries[k] = static_cast<uint16_t>(DW);   // slot row 0 into the spare register
 }
 
+// LDS of k_list_plan: tables, then lists in the space of what precedes them.
+size_t plan_lds_bytes(int form, size_t D, size_t words, size_t stages) {
+  const size_t lists = (form == kListSuperOrder ? 2 : 1) * stages * S;
+  const size_t first = form == kListDense ? 16 * words : form == kListSuperOrder ? 4 * words : 0;
+  return sizeof(uint32_t) * ((form == kListDense ? 4 * words + 2 * D : 2 * words) + (lists > first ? lists : first));
+}
+
 }  // namespace
 
 hipError_t launch_list_plan(const int32_t* indptr, const int32_t* indices, int64_t B, int64_t F,
@@ -447,16 +454,14 @@ hipError_t launch_list_plan(const int32_t* indptr, const int32_t* indices, int64
   hipLaunchKernelGGL(k_list_scan, dim3(1), dim3(1024), 0, stream, tile_count, ntiles, tile_offset, super, nsuper);
   const int32_t words = static_cast<int32_t>((F + 31) / 32);
   const size_t stages = static_cast<size_t>((F + R - 1) / R);
-  // tables, then lists in the space of what precedes them (see k_list_plan)
-  const size_t w = static_cast<size_t>(words), lists = (nsuper ? 2 : 1) * stages * S;
-  const size_t first = form == kListDense ? 16 * w : nsuper ? 4 * w : 0;
-  const size_t bytes = sizeof(uint32_t) * ((form == kListDense ? 4 * w + 2 * D : 2 * w) + (lists > first ? lists : first));
+  const size_t bytes = plan_lds_bytes(form, D, words, stages);
   auto* kernel = DW == 16                ? &k_list_plan<16, kListPlain>
                  : form == kListDense      ? &k_list_plan<32, kListDense>
                  : form == kListSuperOrder ? &k_list_plan<32, kListSuperOrder>
                                            : &k_list_plan<32, kListPlain>;
-  const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kernel),
-                                           hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(bytes));
+  const size_t most = plan_lds_bytes(form, D, form == kListDense ? kListDenseMaxF / 32 : kListMaxF / 32,
+                                     form == kListDense ? kListDenseMaxF / R : kListMaxF / R);
+  const hipError_t e = allow_lds(kernel, most);
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL(kernel, dim3(static_cast<uint32_t>(ntiles)), dim3(kThreads), bytes, stream, indptr, indices, perm,
                      B, words, tile_offset, tile_count, data, start, super, nsuper, phase_wgs);

@@ -64,8 +64,8 @@ __global__ void k_taps(double sigma, int R, float* __restrict__ g) {
 // terms in the same order, k = -R..R.
 constexpr int kOut = 8;   // outputs per thread
 
-// One step of the window: output i's tap k reads cell i + k of the window's
-// start; WIN holds kOut cells, rotated by the unrolled loop.
+// Output i's tap j reads cell i + j of the window's start; w holds the kOut cells of
+// a tap, rotated by the unrolled loop.
 template <typename READ>
 __device__ __forceinline__ void blur_window(const float* taps, int n, float (&out)[kOut], READ read) {
   // taps[0..n-1]; out[i] = sum_j taps[j] * read(i + j), j ascending
@@ -232,12 +232,6 @@ k_blur_cols_tall(const float* __restrict__ t, int64_t ld_t, int rows, int cols, 
 
 constexpr size_t kLdsBytes = 160 * 1024;   // per workgroup
 
-template <typename F>
-hipError_t allow_lds(F* kernel, size_t bytes) {
-  return hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize,
-                             static_cast<int>(bytes));
-}
-
 hipError_t launch_blur_rows(const uint32_t* in, int64_t ld_in, float* out, int64_t ld_out, int rows, int cols, int R,
                             const float* g, int64_t planes, hipStream_t stream) {
   const int Re = R < cols - 1 ? R : cols - 1;
@@ -249,7 +243,7 @@ hipError_t launch_blur_rows(const uint32_t* in, int64_t ld_in, float* out, int64
   while (per > 1 && per * row + taps > 64 * 1024) --per;
   if (per > rows) per = rows;
   const size_t lds = per * row + taps;
-  const hipError_t e = allow_lds(&k_blur_rows<uint32_t>, lds);
+  const hipError_t e = allow_lds(&k_blur_rows<uint32_t>, kLdsBytes);
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL(k_blur_rows<uint32_t>, dim3(static_cast<uint32_t>((rows + per - 1) / per), static_cast<uint32_t>(planes)),
                      dim3(256), lds, stream, in, ld_in, out, ld_out, rows, cols, Re, per, g);
@@ -268,18 +262,18 @@ hipError_t launch_blur_cols(const float* t, int64_t ld_t, int rows, int cols, in
   const size_t narrow = taps + sizeof(float) * cells * blur_col_stride<16>();
   const uint32_t np = static_cast<uint32_t>(planes);
   if (wide <= kLdsBytes / 2 || (wide <= kLdsBytes && narrow > kLdsBytes / 2)) {
-    const hipError_t e = allow_lds(&k_blur_cols<WT, MODE, 32>, wide);
+    const hipError_t e = allow_lds(&k_blur_cols<WT, MODE, 32>, kLdsBytes);
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL((k_blur_cols<WT, MODE, 32>), dim3(static_cast<uint32_t>((cols + 31) / 32), np), dim3(kColThreads), wide,
                        stream, t, ld_t, rows, cols, Re, g, den_out, den, W, ldw);
   } else if (narrow <= kLdsBytes) {
-    const hipError_t e = allow_lds(&k_blur_cols<WT, MODE, 16>, narrow);
+    const hipError_t e = allow_lds(&k_blur_cols<WT, MODE, 16>, kLdsBytes);
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL((k_blur_cols<WT, MODE, 16>), dim3(static_cast<uint32_t>((cols + 15) / 16), np), dim3(kColThreads),
                        narrow, stream, t, ld_t, rows, cols, Re, g, den_out, den, W, ldw);
   } else {
     const size_t tall = sizeof(float) * static_cast<size_t>(rows) * kStrip;
-    const hipError_t e = allow_lds(&k_blur_cols_tall<WT, MODE>, tall);
+    const hipError_t e = allow_lds(&k_blur_cols_tall<WT, MODE>, kLdsBytes);
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL((k_blur_cols_tall<WT, MODE>), dim3(static_cast<uint32_t>((cols + kStrip - 1) / kStrip), np),
                        dim3(256), tall, stream, t, ld_t, rows, cols, R, g, den_out, den, W, ldw);
