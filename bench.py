@@ -61,8 +61,8 @@ MEASURED_TRAFFIC = {
     json.dumps(["map512x512-F20000-2M", [0, 1], 0, 262208, "f32", False, False, False, False,
                 {"group_tiles": 0, "kernel": 0, "lane_neurons": 0, "mask_mode": 0, "neuron_chunk": 0,
                  "schedule": 0, "slice_neurons": 0, "storage": 0, "sweep": 0, "tile_docs": 0}]): {
-        "csrc": "3e480e1ba5bfe47d",
-        "fetch_kib": [2.7669e9, 2.5930e9],       # per search launch (batch 0, batch 1)
+        "csrc": "f588a96b9013c765",
+        "fetch_kib": [2.7512e9, 2.5992e9],       # per search launch (batch 0, batch 1)
         "write_kib": [8.1943e4, 7.4331e4],
         "fetch_scale": 2.0, "write_scale": 1.0,   # plain 4 GiB device copy: FETCH_SIZE reads half, WRITE_SIZE exact
         "source": "rocprofv3 --pmc FETCH_SIZE, then WRITE_SIZE, k_search_list<float,32>, "

@@ -63,12 +63,14 @@ typedef enum som_status {
  * Automatic choices (measured on MI355X at map sizes 32^2 to 512^2, F =
  * 2,048 to 20,000, batches up to 1M documents): rotated union sweeps
  * (`sweep`) wherever available.  With no knob naming a kernel or a geometry:
- * batches of up to 512 documents (fp16: 64) take kernel 1 with two-document tiles
- * in ascending order; fp32 batches of 1,536 documents and more (fp16: 65,536) over
- * at most 65,536 features take the list form of kernel 3, whose plan holds, per
- * tile of 256 documents (fp16: 128) and wave, lists of the (row, document)
- * memberships; it lives in the bytes of the kernel it stands in for.  Otherwise
- * (a knob given, a larger vocabulary, batches between): for an fp32
+ * batches of up to 512 documents (fp16: 64; half of that for plans and on maps of
+ * more than 12,288, fp16 65,536, neurons) take kernel 1 with two-document tiles in
+ * ascending order; batches of 65,536 documents and more over at most 65,536
+ * features, and fp32 searches that plan inside the call of up to 5,120 (12,288 on
+ * maps of up to 16,384 neurons), take the list form of kernel 3, whose plan
+ * holds, per tile of 256 documents (fp16: 128) and wave, lists of the (row,
+ * document) memberships; it lives in the bytes of the kernel it stands in for.
+ * Otherwise (a knob given, a larger vocabulary, batches between): for an fp32
  * codebook kernel 3 with 64-document super-tiles and the document-major
  * dispatch; for fp16, or when a knob only kernel 1 has is set (tile_docs of 32
  * or less, lane_neurons, group_tiles), kernel 1 with tiles of 16 documents for

@@ -84,6 +84,7 @@ struct Plan {
   int schedule = 1;          // 1 = one launch, 2 = round-synchronised launches (kernel 3)
   int chunk_slices = 1;      // kernels 1 and 3: neuron slices per schedule chunk
   bool rotate = false;       // kernel 3: rotated union sweeps (opts->sweep)
+  bool small = false;        // two-document tiles (see small_batch)
   int list_docs = 0;         // > 0: the list form, documents per wave (see choose_lists)
   int list_form = som::kListPlain;
 };
@@ -106,16 +107,32 @@ bool no_geometry(const som_bmu_opts& o) {
 // most of it idle and each of their workgroups a long chain of stages; its plan is
 // short too.  The line is where the larger tiles' rotated sweeps start to rotate:
 // up to eight of them, one per XCD, all have phase 0, so both sum in ascending
-// order and give the same bits.
+// order and give the same bits; on larger maps, where the work of a few tiles
+// fills the device, and for plans, which do not know the map, half of that.
+// Whole calls, F = 20,000, poisson / lognormal documents, in us (the larger tiles
+// against two-document ones): fp32, 512 documents on 32^2 267 against 52, on 96^2
+// 314 / 344 against 138 / 192, on 256^2 828 / 923 against 710 / 1,039, on 512^2
+// 2,926 / 3,049 against 3,033 / 4,139; 256 on 512^2 2,445 / 2,774 against 1,748 /
+// 2,304.  (520 documents in the list form, below: 128^2 195 / 208; 512 here: 268 /
+// 321.)  fp16, 64 documents on 256^2 132 against 107, on 512^2 323 / 452 against
+// 340 / 504; 32 on 512^2 291 / 434 against 200 / 397.
 constexpr int64_t kSmallDocsF32 = 8 * 64, kSmallDocsF16 = 8 * 8;
+constexpr int64_t kSmallMaxNF32 = 12288, kSmallMaxNF16 = 65536;
 constexpr int kSmallTileDocs = 2;
+
+bool small_batch(const som_bmu_opts& o, int64_t N, int64_t B, bool f16, bool planned) {
+  const int64_t most = f16 ? kSmallDocsF16 : kSmallDocsF32;
+  const bool large = planned || N > (f16 ? kSmallMaxNF16 : kSmallMaxNF32);
+  return no_geometry(o) && B <= (large ? most / 2 : most);
+}
 
 // `weights` is the storage type of the codebook searched (it fixes the load
 // width K); `auto_weights` the one the automatic tile size is chosen for:
 // the entry point's own type when it plans internally, opts->storage for
-// som_plan and the planned searches, so that a plan and its search always
-// resolve the same tile geometry.
-som_status make_plan(int64_t N, int64_t B, const som_bmu_opts* opts, Plan* p, int weights, int auto_weights) {
+// som_plan and the planned searches (`planned`), so that a plan and its search
+// always resolve the same tile geometry.
+som_status make_plan(int64_t N, int64_t B, const som_bmu_opts* opts, Plan* p, int weights, int auto_weights,
+                     bool planned) {
   som_bmu_opts o{};
   if (opts) o = *opts;
   const bool f16 = weights == som::kWeightsF16;
@@ -125,12 +142,13 @@ som_status make_plan(int64_t N, int64_t B, const som_bmu_opts* opts, Plan* p, in
   if (o.validate != 0 && o.validate != 1) return fail(SOM_ERR_INVALID_ARG, "opts->validate must be 0 or 1");
   if (o.schedule < 0 || o.schedule > 2) return fail(SOM_ERR_INVALID_ARG, "opts->schedule must be 0, 1 or 2");
   if (o.kernel < 0 || o.kernel > 3) return fail(SOM_ERR_INVALID_ARG, "opts->kernel must be 0, 1, 2 or 3");
-  // automatic kernel: the shared-union super-tiles (kernel 3) for an fp32
-  // codebook, measured faster at every map size from 32^2 to 512^2 and on the
-  // topic workload; kernel 1 for fp16 (8-document tiles, measured faster
-  // there) and whenever a knob only kernel 1 has is given
+  // automatic kernel, where neither small tiles nor the list form (choose_lists)
+  // are taken: the shared-union super-tiles (kernel 3) for an fp32 codebook,
+  // faster than kernel 1 from 32^2 to 512^2 and on the topic workload; kernel 1
+  // for fp16 (8-document tiles, faster there) and whenever a knob only kernel 1
+  // has is given
   const bool k1_knob = (o.tile_docs > 0 && o.tile_docs <= 32) || o.lane_neurons || o.group_tiles;
-  const bool small = no_geometry(o) && B <= (auto16 ? kSmallDocsF16 : kSmallDocsF32);
+  const bool small = small_batch(o, N, B, auto16, planned);
   const int kernel = o.kernel ? o.kernel : ((auto16 || k1_knob || small) ? 1 : 3);
   p->kernel = kernel;
   if (kernel == 1) {
@@ -153,7 +171,9 @@ som_status make_plan(int64_t N, int64_t B, const som_bmu_opts* opts, Plan* p, in
     p->T = T;
     p->K = K;
     p->group = G;
-    p->mask_mode = o.mask_mode == 2 ? 1 : (o.mask_mode == 1 ? 0 : (T <= 4 ? 0 : 1));
+    // (small batches by branches, like the larger tiles they stand in for: no
+    // product of a document's 0 with another's row; the same time)
+    p->mask_mode = o.mask_mode == 2 ? 1 : (o.mask_mode == 1 ? 0 : (T <= 4 && !small ? 0 : 1));
     p->D = T;
     p->nchunks = (N + 64 * K - 1) / (64 * K);
   } else if (kernel == 3) {
@@ -218,6 +238,7 @@ som_status make_plan(int64_t N, int64_t B, const som_bmu_opts* opts, Plan* p, in
                 "one-slice chunks (schedule 1)");
   // (small batches: every phase of the larger tiles that they stand in for is 0)
   p->rotate = (o.sweep == 2 || (o.sweep == 0 && can_rotate)) && !small;
+  p->small = small;
   p->nunits = (B + p->D - 1) / p->D;
   if (p->nunits >= kMaxTiles)
     return fail(SOM_ERR_INVALID_ARG, "batch too large for one launch: too many tiles or groups");
@@ -280,35 +301,48 @@ PlanLayout plan_layout(const Plan& p, int64_t nnz) {
   return l;
 }
 
-// The automatic launch takes the list form of the shared-union search wherever
+// The automatic launch takes the list form of the shared-union search, wherever
 // its plan fits the bytes of the kernel it stands in for (so buffer sizes do not
-// depend on the choice):
-//   fp32, tiles of 256 documents, from kListMinDocs documents on (below, too few
-//     workgroups fill the device: a 2,048-document batch took 0.53 ms on the 128^2
-//     map and 1.79 ms on 256^2 against kernel 3's 0.74 and 2.19, 1,024 documents
-//     0.52 and 1.79 against 0.48 and 1.25).  Up to kListOwnOrderDocs documents it
-//     sums in kernel 3's order (the same bits), from there on in the order that
-//     is fastest for it, with the dense rows first;
-//   fp16, tiles of 128 documents, from kListOwnOrderDocs documents on, in its own
-//     order (kernel 1 below: its eight-document tiles each have a phase).
-// Sums in another order swap about 2.5 units per million documents (fp16: 0.7),
-// over maps of 900 to 262,144 neurons, the three workload laws and both codebooks,
-// and in a few batches some times more; in small batches that can be more than one
-// document in 10,000 (23 of 9,337 drawn batches, the largest of 18,623 documents,
-// and 3 units of one of 32,877), from kListOwnOrderDocs on it was 4e-5 at most.
-// The choice depends on the batch and F only, not on N, so that a plan serves any
-// codebook and column ranges of one compose exactly.  Any kernel or geometry knob
-// keeps the named kernel.
-constexpr int64_t kListMinDocs = 1536, kListOwnOrderDocs = 65536;
+// depend on the choice),
+//   from kListOwnDocs documents on, in the order that is fastest for it (fp32: tiles
+//     of 256 documents, dense rows first; fp16: of 128);
+//   for fp32 searches that plan inside the call, also from the end of the small
+//     batches up to kListSuperMost documents (kListSuperMostSmall on small maps),
+//     in kernel 3's order: the same bits.
+// The order matters because a sum in another one swaps about 2.5 units per million
+// documents (fp16: 0.7), over maps of 900 to 262,144 neurons, the three workload
+// laws and both codebooks, and in a few batches some times more; in small batches
+// that can be more than one document in 10,000 (23 of 9,337 drawn batches, the
+// largest of 18,623 documents, and 3 units of one of 32,877), from kListOwnDocs on
+// it was 4e-5 at most.  There the list form was faster than kernel 3 (fp16: 1) in
+// all of 291 settings (32^2 to 400^2, the three laws, planned and not, ordered and
+// not), by 1.03 to 2 times.
+// Kernel 3's order costs the list form its dense rows and its own phases.  Whole
+// calls at F = 20,000 and 4,999, kernel 3's time over this, poisson and lognormal
+// documents / topics: 400 to 900 documents 1.1-2.6 / 1.4-3.8, 1,024 1.13-1.54 /
+// 1.4-2.4, 2,048 on 32^2 to 128^2
+// 1.02-1.43 / 1.3-1.9, on 180^2 to 512^2 0.91-1.25 / 1.4-1.7, 5,000 1.03-1.36 /
+// 1.4-2.3, 10,000 on 32^2 to 128^2 0.95-1.48 / 1.4-2, on 180^2 to 512^2 0.81-1.06
+// / 1.5; 20,000 on 96^2 and 128^2 0.91-1.05 / 1.3-1.8.  Planned searches, which
+// save only the sweep's part of that, 0.80-1.1 / 0.9-1.4 on 32^2 and 64^2: they keep
+// kernel 3, as a plan does not know the map.
+// Any kernel or geometry knob keeps the named kernel.
+constexpr int64_t kListOwnDocs = 65536;
+constexpr int64_t kListSuperMost = 5120, kListSuperMostSmall = 12288, kListSuperSmallN = 16384;
 
-void choose_lists(int64_t F, int64_t B, int64_t nnz, const som_bmu_opts* opts, int auto_weights, Plan* p) {
+void choose_lists(int64_t F, int64_t N, int64_t B, int64_t nnz, const som_bmu_opts* opts, int auto_weights,
+                  bool planned, Plan* p) {
   som_bmu_opts o{};
   if (opts) o = *opts;
-  if (!no_geometry(o)) return;
+  if (!no_geometry(o) || F > som::kListMaxF) return;
   const bool f16 = auto_weights == som::kWeightsF16;
-  if (F > som::kListMaxF || B < (f16 ? kListOwnOrderDocs : kListMinDocs)) return;
+  int form = p->rotate ? som::kListDense : som::kListPlain;
+  if (B < kListOwnDocs) {
+    const int64_t most = N <= kListSuperSmallN ? kListSuperMostSmall : kListSuperMost;
+    if (f16 || planned || p->small || !p->rotate || B > most) return;
+    form = som::kListSuperOrder;
+  }
   const int docs = f16 ? 16 : 32;
-  const int form = !p->rotate ? som::kListPlain : B < kListOwnOrderDocs ? som::kListSuperOrder : som::kListDense;
   if (list_layout(B, nnz, docs, form).total > plan_layout(*p, nnz).total) return;
   p->list_docs = docs;
   p->list_form = form;
@@ -495,19 +529,20 @@ som_status som_codebook_norms_f16(const uint16_t* W, int64_t F, int64_t N, int64
 // both (an fp16 tile plan has more, smaller tiles).
 static size_t search_ws_bytes(int64_t N, int64_t B, int64_t nnz, const som_bmu_opts* opts) {
   size_t need = 0;
-  for (int w : {som::kWeightsF32, som::kWeightsF16}) {
-    Plan p;
-    if (make_plan(N, B, opts, &p, w, w) != SOM_OK) continue;
-    const size_t t = search_ws(p, B, nnz, opts && opts->validate).total;
-    need = t > need ? t : need;
-  }
+  for (int w : {som::kWeightsF32, som::kWeightsF16})
+    for (bool planned : {false, true}) {   // either side of the map's line (small_batch)
+      Plan p;
+      if (make_plan(N, B, opts, &p, w, w, planned) != SOM_OK) continue;
+      const size_t t = search_ws(p, B, nnz, opts && opts->validate).total;
+      need = t > need ? t : need;
+    }
   return need;
 }
 
 size_t som_bmu_workspace_bytes(int64_t F, int64_t N, int64_t B, int64_t nnz, const som_bmu_opts* opts) {
   if (F < 1 || N < 1 || B < 0 || nnz < 0) return 0;
   Plan p;
-  if (make_plan(N, B, opts, &p, som::kWeightsF32, som::kWeightsF32) != SOM_OK) return 0;
+  if (make_plan(N, B, opts, &p, som::kWeightsF32, som::kWeightsF32, false) != SOM_OK) return 0;
   return search_ws_bytes(N, B, nnz, opts);
 }
 
@@ -524,7 +559,7 @@ static som_status search_impl(const void* W, int weights, int64_t F, int64_t N, 
   if (B > 0 && (!bmu || !dist)) return fail(SOM_ERR_INVALID_ARG, "bmu or dist is NULL");
   if (top2 && B > 0 && (!bmu2 || !dist2)) return fail(SOM_ERR_INVALID_ARG, "bmu2 or dist2 is NULL");
   Plan p;
-  s = make_plan(N, B, opts, &p, weights, weights);
+  s = make_plan(N, B, opts, &p, weights, weights, false);
   if (s != SOM_OK) return s;
   const bool validate = opts && opts->validate;
   const SearchWs w = search_ws(p, B, nnz, validate);
@@ -537,7 +572,7 @@ static som_status search_impl(const void* W, int weights, int64_t F, int64_t N, 
     s = run_validate(indptr, indices, B, F, nnz, perm, at<int32_t>(ws, w.seen), at<int32_t>(ws, w.flag), stream);
     if (s != SOM_OK) return s;
   }
-  choose_lists(F, B, nnz, opts, weights, &p);
+  choose_lists(F, N, B, nnz, opts, weights, false, &p);
   const PlanLayout l = used_layout(p, B, nnz);
   hipError_t e = build_plan(indptr, indices, B, F, perm, p, ws, l, stream);
   if (e != hipSuccess) return hip_fail(e, "plan launch");
@@ -609,7 +644,7 @@ som_status som_bmu_search_noalloc(const float* W, int64_t F, int64_t N, int64_t 
   if (opts && opts->validate)
     return fail(SOM_ERR_INVALID_ARG, "validate synchronises the stream: not available on the allocation-free search");
   Plan p;
-  s = make_plan(N, B, opts, &p, som::kWeightsF32, som::kWeightsF32);
+  s = make_plan(N, B, opts, &p, som::kWeightsF32, som::kWeightsF32, false);
   if (s != SOM_OK) return s;
   const size_t need = search_ws(p, B, nnz, false).total;
   if (need > SOM_NOALLOC_SCRATCH_BYTES)
@@ -658,7 +693,7 @@ size_t som_plan_bytes(int64_t B, int64_t nnz, const som_bmu_opts* opts) {
   if (B < 0 || nnz < 0) return 0;
   Plan p;
   const int st = opts_storage(opts);
-  if (make_plan(1, B, opts, &p, st, st) != SOM_OK) return 0;
+  if (make_plan(1, B, opts, &p, st, st, true) != SOM_OK) return 0;
   return plan_layout(p, nnz).total;
 }
 
@@ -671,7 +706,7 @@ som_status som_plan(const int32_t* indptr, const int32_t* indices, int64_t B, in
   if (opts && opts->validate) return fail(SOM_ERR_INVALID_ARG, "validate applies to som_bmu_search only");
   Plan p;
   const int st = opts_storage(opts);
-  s = make_plan(1, B, opts, &p, st, st);
+  s = make_plan(1, B, opts, &p, st, st, true);
   if (s != SOM_OK) return s;
   const PlanLayout l = plan_layout(p, nnz);
   if (B == 0) return ok();
@@ -679,7 +714,7 @@ som_status som_plan(const int32_t* indptr, const int32_t* indices, int64_t B, in
   if (!aligned(plan, 256)) return fail(SOM_ERR_INVALID_ARG, "plan must be 256-byte aligned");
   if (plan_bytes < l.total)
     return fail(SOM_ERR_WORKSPACE, "plan buffer too small: need " + std::to_string(l.total) + " bytes");
-  choose_lists(F, B, nnz, opts, st, &p);
+  choose_lists(F, 1, B, nnz, opts, st, true, &p);
   hipError_t e = build_plan(indptr, indices, B, F, perm, p, plan, used_layout(p, B, nnz), stream);
   if (e != hipSuccess) return hip_fail(e, "plan launch");
   return ok();
@@ -688,7 +723,7 @@ som_status som_plan(const int32_t* indptr, const int32_t* indices, int64_t B, in
 size_t som_bmu_search_planned_workspace_bytes(int64_t N, int64_t B, const som_bmu_opts* opts) {
   if (N < 1 || B < 0) return 0;
   Plan p;
-  if (make_plan(N, B, opts, &p, opts_storage(opts), opts_storage(opts)) != SOM_OK) return 0;
+  if (make_plan(N, B, opts, &p, opts_storage(opts), opts_storage(opts), true) != SOM_OK) return 0;
   return keys_bytes(B);
 }
 
@@ -704,7 +739,7 @@ static som_status planned_impl(const void* W, int weights, int64_t F, int64_t N,
   if (nnz < 0 || nnz > kI32Max) return fail(SOM_ERR_INVALID_ARG, "nnz must be in [0, 2^31)");
   if (opts && opts->validate) return fail(SOM_ERR_INVALID_ARG, "validate is not available on a planned search");
   Plan p;
-  s = make_plan(N, B, opts, &p, weights, opts_storage(opts));
+  s = make_plan(N, B, opts, &p, weights, opts_storage(opts), true);
   if (s != SOM_OK) return s;
   const PlanLayout l = plan_layout(p, nnz);
   if (B == 0) return ok();
@@ -720,7 +755,7 @@ static som_status planned_impl(const void* W, int weights, int64_t F, int64_t N,
   // the form som_plan chose: its F is at most this one, so up to kListMaxF both
   // choices agree; beyond, the plan may be a list plan (of a smaller F) or not
   Plan q = p;
-  choose_lists(F < som::kListMaxF ? F : som::kListMaxF, B, nnz, opts, opts_storage(opts), &q);
+  choose_lists(F < som::kListMaxF ? F : som::kListMaxF, N, B, nnz, opts, opts_storage(opts), true, &q);
   const bool either = q.list_docs && F > som::kListMaxF;
   const PlanLayout ql = used_layout(q, B, nnz);
   return run_planned(W, weights, F, N, ldw, norms, indptr, B, perm, plan, ql, bmu, dist, top2 ? bmu2 : nullptr, dist2, q,
@@ -866,7 +901,7 @@ static som_status unfused_plan(int64_t N, int64_t B, const som_bmu_opts* opts, i
   som_bmu_opts o{};
   if (opts) o = *opts;
   if (o.kernel == 0) o.kernel = 1;
-  som_status s = make_plan(N, B, &o, p, som::kWeightsF32, som::kWeightsF32);
+  som_status s = make_plan(N, B, &o, p, som::kWeightsF32, som::kWeightsF32, false);
   if (s != SOM_OK) return s;
   if (p->kernel != 1) return fail(SOM_ERR_INVALID_ARG, "the unfused comparator uses kernel 1");
   if (o.sweep == 2) return fail(SOM_ERR_INVALID_ARG, "the unfused comparator sweeps in ascending order (sweep 0 or 1)");

@@ -426,9 +426,13 @@ k_search_list(SearchArgs a) {
 
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  // XCD-contiguous tile ranges, slice-major (see k_search)
+  // XCD-contiguous tile ranges, slice-major (see k_search).  SUPER: the tiles are
+  // few, and whole ranges of them per XCD would leave some XCDs with less, or
+  // nothing; dealt out tile by tile over all slices, each XCD gets its share (2,560
+  // documents on 256^2: ranges 0.77 of kernel 3's speed, dealt out 1.16)
   const uint32_t per_xcd = gridDim.x / kXcds;
-  const int64_t t = static_cast<int64_t>(blockIdx.x % kXcds) * per_xcd + blockIdx.x / kXcds;
+  const int64_t t = SUPER ? static_cast<int64_t>(blockIdx.x)
+                          : static_cast<int64_t>(blockIdx.x % kXcds) * per_xcd + blockIdx.x / kXcds;
   if (t >= a.ntiles) return;  // whole workgroup: no barrier is skipped by part of it
   if (a.either && !(static_cast<uint32_t>(a.tile_offset[0]) & kListTag)) return;  // a tile plan
   const int64_t n0 = (a.slice_base + blockIdx.y) * WN;
@@ -566,8 +570,9 @@ k_search_list(SearchArgs a) {
 
 template <typename WT, int DW, bool TOP2, bool WIDE>
 void launch_list_grid(const SearchArgs& a, dim3 grid, hipStream_t stream) {
-  if constexpr (DW == 32) {
+  if constexpr (DW == 32 && sizeof(WT) == 4) {
     if (a.rotate == 2) {
+      grid.x = static_cast<uint32_t>(a.ntiles);
       hipLaunchKernelGGL((k_search_list<WT, DW, TOP2, WIDE, true>), grid, dim3(kListWaves * 64), 0, stream, a);
       return;
     }

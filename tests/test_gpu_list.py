@@ -1,6 +1,6 @@
 """GPU checks of the automatic launch's list form (tiles of 256 documents for
 fp32, 128 for fp16; per-wave entry lists) at the sizes where it can go wrong:
-the batch sizes its forms start at (fp32: 1,536 documents, in kernel 3's order, and
+the batch sizes its forms start at (fp32: 513 documents, in kernel 3's order, and
 65,536, in its own; fp16: 65,536) and ragged last tiles, unions of one stage and of
 one row more, documents with no feature and with more than two 64-lane reads of
 them, maps around the slice width, the largest vocabulary it takes, rows of 4 GB
@@ -24,7 +24,7 @@ else:  # collected on CPU-only machines, never run there
 
 DEV = "cuda:0"
 # batches from which a form of the list kernel is taken
-FORMS = [(np.float32, 1536), (np.float32, 65536), (np.float16, 65536)]
+FORMS = [(np.float32, 513), (np.float32, 65536), (np.float16, 65536)]
 
 
 def _csr(key, B, F):
