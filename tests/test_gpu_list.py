@@ -56,6 +56,18 @@ def _book(rng, F, N, dtype, ldw=None, dyadic=True):
     return W, som.som_codebook_norms(W, N=N)
 
 
+def _auto(top2, W, norms, ip, ix, N, perm=None, sweep=0):
+    """The automatic search, and that it took the list form where it should: its
+    plan, at the start of the workspace, then bears the list plan's mark."""
+    B, F = ip.numel() - 1, W.shape[0]
+    ws = torch.empty(som.som_bmu_workspace_bytes(F, N, B, ix.numel(), sweep=sweep), dtype=torch.uint8, device=DEV)
+    got = (som.som_bmu_search_top2 if top2 else som.som_bmu_search)(W, norms, ip, ix, N=N, perm=perm, ws=ws, sweep=sweep)
+    listed = F <= 65536 and (B >= 65536 or (W.dtype == torch.float32 and sweep != 1 and 512 < B <= 12288))
+    if F > 1:      # (one feature: the list plan does not fit the fp16 tile plan's bytes)
+        assert (int(ws[:4].view(torch.int32)) < 0) == listed
+    return got
+
+
 def _equal(a, b):
     return all(torch.equal(x, y) for x, y in zip(a, b))
 
@@ -72,9 +84,8 @@ def test_list_form_matches_kernel_1(dtype, least, extra, F, N):
     for p in (None, perm):
         want = som.som_bmu_search_top2(W, norms, ip, ix, N=N, perm=p, kernel=1, sweep=1)
         for sweep in (0, 1):
-            got = som.som_bmu_search_top2(W, norms, ip, ix, N=N, perm=p, sweep=sweep)
-            assert _equal(got, want), (sweep, p is None)
-            assert _equal(som.som_bmu_search(W, norms, ip, ix, N=N, perm=p, sweep=sweep), want[:2]), sweep
+            assert _equal(_auto(True, W, norms, ip, ix, N, p, sweep), want), (sweep, p is None)
+            assert _equal(_auto(False, W, norms, ip, ix, N, p, sweep), want[:2]), sweep
 
 
 @pytest.mark.parametrize("dtype", [np.float32, np.float16])
@@ -125,7 +136,25 @@ def test_list_form_rows_of_4_gib():
     ip, ix = _docs(rng, B, F)
     W, norms = _book(rng, F, N, np.float32, ldw=(1 << 30) + 64)
     want = som.som_bmu_search_top2(W, norms, ip, ix, N=N, kernel=1, sweep=1)
-    assert _equal(som.som_bmu_search_top2(W, norms, ip, ix, N=N), want)
+    assert _equal(_auto(True, W, norms, ip, ix, N), want)
+    assert _equal(_auto(False, W, norms, ip, ix, N), want[:2])
+
+
+def test_list_form_on_more_slices_than_one_launch_takes():
+    # 128-neuron slices: a grid holds 65,535 of them, a wider map takes two
+    rng = np.random.default_rng(13)
+    F, N, B = 2, 65535 * 128 + 300, 520
+    ip, ix = _docs(rng, B, F)
+    W = torch.zeros((F, som.som_codebook_ldw(N)), device=DEV)
+    W[0, :N] = (torch.arange(N, device=DEV) % 4096) / 4096      # dyadic, the minima in the last slices
+    W[1, :N] = 1.0
+    W[:, N - 200:N - 1] = torch.tensor([[0.75], [0.5]], device=DEV)
+    norms = som.som_codebook_norms(W, N=N)
+    norms[N - 200:] -= 2.0                                       # (norms are an input: these units win)
+    want = som.som_bmu_search_top2(W, norms, ip, ix, N=N, kernel=1, sweep=1)
+    assert int(want[0].min()) > 65535 * 128
+    got = som.som_bmu_search_top2(W, norms, ip, ix, N=N)
+    assert _equal(got, want)
     assert _equal(som.som_bmu_search(W, norms, ip, ix, N=N), want[:2])
 
 
@@ -152,9 +181,8 @@ def test_rows_that_many_documents_hold(dtype, least, dense, share, F):
             norms[:N:3] *= 0.5
         want = som.som_bmu_search_top2(W, norms, ip, ix, N=N, kernel=1, sweep=1)
         for sweep in (0, 1):
-            got = som.som_bmu_search_top2(W, norms, ip, ix, N=N, sweep=sweep)
-            assert _equal(got, want), (special, sweep)
-            assert _equal(som.som_bmu_search(W, norms, ip, ix, N=N, sweep=sweep), want[:2]), (special, sweep)
+            assert _equal(_auto(True, W, norms, ip, ix, N, sweep=sweep), want), (special, sweep)
+            assert _equal(_auto(False, W, norms, ip, ix, N, sweep=sweep), want[:2]), (special, sweep)
 
 
 @pytest.mark.parametrize("dtype,least", FORMS)
@@ -169,8 +197,8 @@ def test_what_lies_between_the_rows_is_never_a_unit(dtype, least, N):
     W[:, N:].view(torch.int16 if dtype == np.float16 else torch.int32).fill_(-1)
     want = som.som_bmu_search_top2(W, norms, ip, ix, N=N, kernel=1, sweep=1)
     for sweep in (0, 1):
-        assert _equal(som.som_bmu_search_top2(W, norms, ip, ix, N=N, sweep=sweep), want), sweep
-        assert _equal(som.som_bmu_search(W, norms, ip, ix, N=N, sweep=sweep), want[:2]), sweep
+        assert _equal(_auto(True, W, norms, ip, ix, N, sweep=sweep), want), sweep
+        assert _equal(_auto(False, W, norms, ip, ix, N, sweep=sweep), want[:2]), sweep
     # where no distance is a number, there is no best unit, but the answer is one of the map
     for bits in (0x7fc00000, -1):
         norms.view(torch.int32).fill_(bits)
