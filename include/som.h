@@ -57,7 +57,7 @@ typedef enum som_status {
  * the ascending sweep every document's dot product is summed in ascending
  * feature order whatever the other knobs, so outputs are bit-identical
  * across all their settings and all kernels; the rotated sweep (the default
- * of kernels 1 and 3) sums in a rotated order that is fixed for a given
+ * of kernel 1, kernel 3 and its list form) sums in a rotated order that is fixed for a given
  * batch, perm, opts and device.
  *
  * Automatic choices (measured on MI355X at map sizes 32^2 to 512^2, F =
@@ -104,7 +104,8 @@ typedef enum som_status {
 typedef struct som_bmu_opts {
   int32_t kernel;        /* 0 = auto (see above), 1 = neurons on lanes, 2 = documents on lanes,
                             3 = shared-union super-tiles */
-  int32_t tile_docs;     /* kernel 1: T = 0 (auto: 16 for fp32, 8 for fp16), 1, 2, 4, 8, 16 or 32;
+  int32_t tile_docs;     /* kernel 1: T = 0 (auto: 16 for fp32, 8 for fp16; 2 where the automatic
+                            launch takes it for a small batch), 1, 2, 4, 8, 16 or 32;
                             kernel 3: D = 0 (auto: 64), 64, 128 or 256 (256: fp32 only) */
   int32_t lane_neurons;  /* kernel 1: K = 0 (auto: 4 for fp32, 8 for fp16), 4 or 8; T = 32 needs 4 */
   int32_t group_tiles;   /* kernel 1: tiles per workgroup, 0 (auto: see above), 1, 2, 4 or 8;
@@ -141,8 +142,8 @@ typedef struct som_bmu_opts {
                             many of a tile's documents hold; on the topic workload measured 19%
                             faster with kernel 3 and 17% with fp16 kernel 1; within 1.3% on
                             the Zipf maps).  A document's dot product is then summed in that
-                            order, which depends on the plan, the launch's tile grid and the
-                            device's CU count, not on the codebook, its storage type or the
+                            order, which depends on the plan, the launch's tile grid and
+                            (the list form's own order excepted) the device's CU count, not on the codebook, its storage type or the
                             neuron range: results are reproducible on one device type, fp16
                             and fp32 searches of one plan use the same order, and column
                             ranges compose exactly, but results may differ from the ascending
@@ -348,12 +349,11 @@ som_status som_cluster_order(const int32_t* indptr, const int32_t* indices, int6
  * weights' norms (fp64 accumulate, rounded once), and every document's dot
  * product sums the widened weights in the order opts->sweep names, so fp16
  * and fp32 searches of the same (fp16-representable) codebook with the same
- * kernel and knobs are bit-identical; across the automatic kernels (3 for
- * fp32, 1 for fp16, both rotating) they are with the ascending sweep
- * (sweep = 1).  Search knobs: kernels 1 (the automatic one for
- * fp16) and 3; lane_neurons 0 or 8 (a 512-neuron slice, one 128-bit load of
- * 8 weights per lane per row); tile_docs up to 16 for kernel 1, 64 or 128
- * for kernel 3.  Plans from som_plan are shared with the fp32 search.
+ * kernel and knobs are bit-identical; across the automatic launches of the two
+ * types, which differ, they are with the ascending sweep (sweep = 1).  Search
+ * knobs: kernels 1 and 3; lane_neurons 0 or 8 (a 512-neuron slice, one 128-bit
+ * load of 8 weights per lane per row); tile_docs up to 16 for kernel 1, 64 or
+ * 128 for kernel 3.  Plans from som_plan are shared with the fp32 search.
  * ------------------------------------------------------------------------- */
 som_status som_codebook_norms_f16(const uint16_t* W, int64_t F, int64_t N, int64_t ldw, float* norms,
                                   hipStream_t stream);

@@ -1,6 +1,7 @@
 // Fused BMU search, kernel 2 (documents on lanes), the key array
-// initialisation and decode, and the dispatch of the three kernels (paper,
-// Section 3; kernel 1 is in search_k1.h, kernel 3 in search_st.h).
+// initialisation and decode, and the dispatch of the kernels (paper, Section 3;
+// kernel 1 is in search_k1.h, kernel 3 in search_st.h, its list form, kernel 4
+// here, in search_list.h).
 #include "search_list.h"
 
 namespace som {

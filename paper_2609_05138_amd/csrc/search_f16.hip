@@ -1,4 +1,4 @@
-// Kernels 1 and 3 of the fused BMU search over an fp16 codebook (the paper's
+// Kernels 1 and 3, and the list form, of the fused BMU search over an fp16 codebook (the paper's
 // storage precision, Sections 4.2 and 4.3): 512-neuron slices (8 neurons per lane, one
 // 128-bit load per row), rows widened to fp32 once per load, fp32 sums.
 #include "search_list.h"

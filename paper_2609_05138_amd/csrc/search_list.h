@@ -16,16 +16,19 @@
 // accumulator is named through the VGPR index register, fold them in.  A
 // unit's reads are issued before the previous unit's adds.
 //
-// What bounds it: vector issue and the LDS reads, three vector instructions and
-// 512 bytes per entry (on the 512^2 map a 262,144-document batch took 523 ms with
-// every row in the lists, about 260 of them in the lists, the rest in stage
-// barriers and the stages' fixed instructions; the row loads alone took 300 ms
-// and overlap; 504 with the rows that many documents hold on the matrix cores).  Kernel 3
-// took 545 ms there: its 64-document tiles of 256-neuron slices need 484 ms of
-// row loads (33.6 rows per document at a working set of 20 MB per slice against
-// 21.7 rows at 10 MB) and a scalar test per document and 16-row stage.  On the
-// 512^2 topic batch, which the row loads bound, 131,072 documents took 449-455 ms
-// (kernel 3: 648); the 128^2 map's 65,536-document pass 8.4 ms (12.0).
+// What bounds it: no one unit.  An entry takes three vector instructions, two or
+// three scalar ones and 512 bytes of LDS reads; on a 1,048,576-document batch of
+// the 512^2 map (2.28 s) vector instructions fill 41% of the CUs' vector issue and
+// scalar ones 37%, the LDS is busy for 21% of the cycles and a SIMD's matrix cores
+// for 5%, and the waves, 16 per CU, wait 55% of their cycles: at the stage barrier,
+// for their LDS reads and for the row loads, which come from the L2 for 78%
+// (fp16: 55, 31, 19, 0 and 54%; topics: 36, 35, 20, 1 and 57%, 68% from the L2).
+// A 262,144-document batch takes 504 ms (523 with every row in the lists; its row
+// loads alone 300, beside the rest).  Kernel 3 took 545 ms there: its 64-document
+// tiles of 256-neuron slices need 484 ms of row loads (33.6 rows per document at a
+// working set of 20 MB per slice against 21.7 rows at 10 MB) and a scalar test per
+// document and 16-row stage.  On the 512^2 topic batch 131,072 documents took
+// 449-455 ms (kernel 3: 648); the 128^2 map's 65,536-document pass 8.4 ms (12.0).
 // Measured and not kept: rows held by one document loaded straight into
 // registers by the document's wave (575 ms: the loads wait for each other, where
 // the staged ones are in flight together), and scalar copies of the next list's

@@ -312,7 +312,7 @@ def som_bmu_search(W: torch.Tensor, norms: torch.Tensor, indptr: torch.Tensor, i
     lane_neurons, group_tiles, mask_mode, slice_neurons, schedule,
     neuron_chunk, sweep (fields of som_bmu_opts; only sweep changes a
     result, in rounding: 1 = ascending feature order, 2 = rotated, the
-    kernel-3 default)."""
+    default wherever it is available)."""
     return _search(False, W, norms, indptr, indices, N, perm, validate, (bmu, dist), ws, stream, knobs)
 
 

@@ -91,3 +91,11 @@ def test_oracle_sample_plan():
     assert np.array_equal(s[0], np.arange(10000))
     s = bench.sample_docs([65536, 65536], 2, [0, 1], 2048)
     assert len(s[0]) == 65536 and len(s[1]) == 1024
+
+
+def test_launch_rule_is_read_back_not_restated():
+    # the library alone holds the lines between its kernels: the benchmark asks
+    # som_plan_bytes and the plans, and names no batch size or vocabulary of the rule
+    src = open(BENCH).read()
+    for number in ("1536", "65536", "12288", "5120"):
+        assert number not in src, number
