@@ -346,3 +346,11 @@ def test_binding_refuses_cpu_tensors(lib):
     W = torch.zeros(4, 4)
     with pytest.raises(ValueError):
         som.som_codebook_norms(W)
+
+
+def test_automatic_workspace_does_not_depend_on_the_map(lib):
+    # the automatic launch may differ with the map (small batches), but one
+    # workspace serves every column range of a codebook
+    for B in (1, 32, 33, 64, 65, 256, 257, 512, 513, 1024, 5120, 5121, 12288, 12289, 65535, 65536, 100000):
+        sizes = {lib.som_bmu_workspace_bytes(20000, N, B, 7 * B, None) for N in (1, 12288, 12289, 16385, 65537, 262144)}
+        assert len(sizes) == 1 and min(sizes) > 0, (B, sizes)
