@@ -315,11 +315,13 @@ PlanLayout plan_layout(const Plan& p, int64_t nnz) {
 // that can be more than one document in 10,000 (23 of 9,337 drawn batches, the
 // largest of 18,623 documents, and 3 units of one of 32,877), from kListOwnDocs on
 // it was 4e-5 at most.  There the list form was faster than kernel 3 (fp16: 1) in
-// all of 291 settings (32^2 to 400^2, the three laws, planned and not, ordered and
-// not), by 1.03 to 2 times.
+// all of 345 settings of up to 700,000 documents (32^2 to 400^2, the three laws,
+// planned and not, ordered and not), by 1.03 to 2 times, and at 1,048,576 by 1.0 to
+// 1.9, but for fp16 on one vocabulary, planned: 0.97 on 64^2, 256^2 and 512^2 (1,568
+// ms there against 1,534; topics 2,248 against 2,670).
 // Kernel 3's order costs the list form its dense rows and its own phases.  Whole
 // calls at F = 20,000 and 4,999, kernel 3's time over this, poisson and lognormal
-// documents / topics: 400 to 900 documents 1.1-2.6 / 1.4-3.8, 1,024 1.13-1.54 /
+// documents / topics: 400 to 900 documents 1.1-2.6 / 1.4-3.9, 1,024 1.10-1.54 /
 // 1.4-2.4, 2,048 on 32^2 to 128^2
 // 1.02-1.43 / 1.3-1.9, on 180^2 to 512^2 0.91-1.25 / 1.4-1.7, 5,000 1.03-1.36 /
 // 1.4-2.3, 10,000 on 32^2 to 128^2 0.95-1.48 / 1.4-2, on 180^2 to 512^2 0.81-1.06
