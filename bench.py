@@ -62,8 +62,8 @@ MEASURED_TRAFFIC = {
     json.dumps(["map512x512-F20000-2M", [0, 1], 0, 262208, "f32", False, False, False, False,
                 {"group_tiles": 0, "kernel": 0, "lane_neurons": 0, "mask_mode": 0, "neuron_chunk": 0,
                  "schedule": 0, "slice_neurons": 0, "storage": 0, "sweep": 0, "tile_docs": 0}]): {
-        "csrc": "7714fa2031f298c0",
-        "fetch_kib": [2.7656e9, 2.5887e9],       # per search launch (batch 0, batch 1)
+        "csrc": "e8d8e830df9d796e",
+        "fetch_kib": [2.7690e9, 2.6013e9],       # per search launch (batch 0, batch 1)
         "write_kib": [8.1943e4, 7.4331e4],
         "fetch_scale": 2.0, "write_scale": 1.0,   # plain 4 GiB device copy: FETCH_SIZE reads half, WRITE_SIZE exact
         "source": "rocprofv3 --pmc FETCH_SIZE, then WRITE_SIZE, k_search_list<float,32>, "
@@ -73,8 +73,8 @@ MEASURED_TRAFFIC = {
     json.dumps(["map512x512-F20000-26.9M-topics", [0], 0, 262208, "f32", False, False, False, False,
                 {"group_tiles": 0, "kernel": 0, "lane_neurons": 0, "mask_mode": 0, "neuron_chunk": 0,
                  "schedule": 0, "slice_neurons": 0, "storage": 0, "sweep": 0, "tile_docs": 0}]): {
-        "csrc": "7714fa2031f298c0",
-        "fetch_kib": [4.8073e9],
+        "csrc": "e8d8e830df9d796e",
+        "fetch_kib": [4.8168e9],
         "write_kib": [10.0397e4],
         "fetch_scale": 2.0, "write_scale": 1.0,
         "source": "rocprofv3 --pmc FETCH_SIZE, then WRITE_SIZE, k_search_list<float,32>, "

@@ -66,8 +66,8 @@ typedef enum som_status {
  * batches of up to 512 documents (fp16: 64; half of that for plans and on maps of
  * more than 12,288, fp16 65,536, neurons) take kernel 1 with two-document tiles in
  * ascending order; batches of 65,536 documents and more over at most 65,536
- * features, and fp32 searches that plan inside the call of up to 5,120 (12,288 on
- * maps of up to 16,384 neurons), take the list form of kernel 3, whose plan
+ * features, and fp32 batches of up to 5,120 (12,288 where the search plans inside
+ * the call, on maps of up to 16,384 neurons), take the list form of kernel 3, whose plan
  * holds, per tile of 256 documents (fp16: 128) and wave, lists of the (row,
  * document) memberships; it lives in the bytes of the kernel it stands in for.
  * Otherwise (a knob given, a larger vocabulary, batches between): for an fp32

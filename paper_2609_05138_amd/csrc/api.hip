@@ -306,9 +306,9 @@ PlanLayout plan_layout(const Plan& p, int64_t nnz) {
 // depend on the choice),
 //   from kListOwnDocs documents on, in the order that is fastest for it (fp32: tiles
 //     of 256 documents, dense rows first; fp16: of 128);
-//   for fp32 searches that plan inside the call, also from the end of the small
-//     batches up to kListSuperMost documents (kListSuperMostSmall on small maps),
-//     in kernel 3's order: the same bits.
+//   for fp32 also from the end of the small batches up to kListSuperMost documents
+//     (planned inside the call, on small maps, kListSuperMostSmall), in kernel 3's
+//     order: the same bits.
 // The order matters because a sum in another one swaps about 2.5 units per million
 // documents (fp16: 0.7), over maps of 900 to 262,144 neurons, the three workload
 // laws and both codebooks, and in a few batches some times more; in small batches
@@ -325,9 +325,9 @@ PlanLayout plan_layout(const Plan& p, int64_t nnz) {
 // 1.4-2.4, 2,048 on 32^2 to 128^2
 // 1.02-1.43 / 1.3-1.9, on 180^2 to 512^2 0.91-1.25 / 1.4-1.7, 5,000 1.03-1.36 /
 // 1.4-2.3, 10,000 on 32^2 to 128^2 0.95-1.48 / 1.4-2, on 180^2 to 512^2 0.81-1.06
-// / 1.5; 20,000 on 96^2 and 128^2 0.91-1.05 / 1.3-1.8.  Planned searches, which
-// save only the sweep's part of that, 0.80-1.1 / 0.9-1.4 on 32^2 and 64^2: they keep
-// kernel 3, as a plan does not know the map.
+// / 1.5; 20,000 on 96^2 and 128^2 0.91-1.05 / 1.3-1.8.  Planned searches, without
+// the plan kernel's share of that, up to 5,000 documents: 0.80-1.0 / 0.9-1.3 on 32^2
+// (10 to 25 us), 0.85-1.5 / 0.9-2.3 on 64^2, 0.90-1.9 / 1.2-2.6 from 96^2 on.
 // Any kernel or geometry knob keeps the named kernel.
 constexpr int64_t kListOwnDocs = 65536;
 constexpr int64_t kListSuperMost = 5120, kListSuperMostSmall = 12288, kListSuperSmallN = 16384;
@@ -340,8 +340,8 @@ void choose_lists(int64_t F, int64_t N, int64_t B, int64_t nnz, const som_bmu_op
   const bool f16 = auto_weights == som::kWeightsF16;
   int form = p->rotate ? som::kListDense : som::kListPlain;
   if (B < kListOwnDocs) {
-    const int64_t most = N <= kListSuperSmallN ? kListSuperMostSmall : kListSuperMost;
-    if (f16 || planned || p->small || !p->rotate || B > most) return;
+    const int64_t most = !planned && N <= kListSuperSmallN ? kListSuperMostSmall : kListSuperMost;
+    if (f16 || p->small || !p->rotate || B > most) return;
     form = som::kListSuperOrder;
   }
   const int docs = f16 ? 16 : 32;

@@ -573,7 +573,7 @@ k_search_list(SearchArgs a) {
 
 template <typename WT, int DW, bool TOP2, bool WIDE>
 void launch_list_grid(const SearchArgs& a, dim3 grid, hipStream_t stream) {
-  if constexpr (DW == 32 && sizeof(WT) == 4) {
+  if constexpr (DW == 32) {
     if (a.rotate == 2) {
       grid.x = static_cast<uint32_t>(a.ntiles);
       hipLaunchKernelGGL((k_search_list<WT, DW, TOP2, WIDE, true>), grid, dim3(kListWaves * 64), 0, stream, a);

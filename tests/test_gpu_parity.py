@@ -666,7 +666,8 @@ def test_planned_search_reuses_a_plan_across_codebooks():
     perm = _dev_i32(oracle.cluster_order(indptr, indices, 2048))
     plan = som.som_plan(ip, ix, 2048, perm=perm, sweep=1)       # kernel 3, ascending sweep
     plan1 = som.som_plan(ip, ix, 2048, perm=perm, kernel=1, tile_docs=4, sweep=1)
-    planr = som.som_plan(ip, ix, 2048, perm=perm)                # kernel 3, rotated sweep
+    planr = som.som_plan(ip, ix, 2048, perm=perm)                # the automatic launch, rotated sweep
+    plan3 = som.som_plan(ip, ix, 2048, perm=perm, kernel=3)      # kernel 3, rotated sweep
     for seed in (0, 1):
         W = codebook(1, seed=seed)
         Wd, _ = _dev_W(W)
@@ -676,8 +677,10 @@ def test_planned_search_reuses_a_plan_across_codebooks():
         c = som.som_bmu_search_planned(Wd, norms, ip, plan1)
         r = som.som_bmu_search_planned(Wd, norms, ip, planr)
         r0 = som.som_bmu_search(Wd, norms, ip, ix, perm=perm)
+        r3 = som.som_bmu_search_planned(Wd, norms, ip, plan3)
         torch.cuda.synchronize()
         assert torch.equal(r[0], r0[0]) and torch.equal(r[1], r0[1])
+        assert torch.equal(r3[0], r0[0]) and torch.equal(r3[1], r0[1])
         assert torch.equal(a[0], c[0]) and torch.equal(a[1], c[1])
         torch.cuda.synchronize()
         assert torch.equal(a[0], b[0]) and torch.equal(a[1], b[1])

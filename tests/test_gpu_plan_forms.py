@@ -41,7 +41,7 @@ def test_plans_serve_codebooks_with_more_rows(F, rows, B, storage, dtype):
     for sweep in (0, 1):
         plan = som.som_plan(ip, ix, F, perm=perm, storage=storage, sweep=sweep)
         listed = int(plan.buf[:4].view(torch.int32)) < 0          # the mark of a list plan
-        assert listed == (F <= 65536 and B >= 65536)
+        assert listed == (F <= 65536 and (B >= 65536 or (storage == 0 and sweep == 0 and 256 < B <= 5120)))
         got = som.som_bmu_search_top2_planned(W, norms, ip, plan, N=N)
         assert all(torch.equal(x, y) for x, y in zip(got, want)), sweep
         best = som.som_bmu_search_planned(W, norms, ip, plan, N=N)
